@@ -124,6 +124,72 @@ RS_DEV unsigned long long wave_min_u64(unsigned long long v) {
     return v;
 }
 
+// value of lane l (uniform) in every lane
+RS_DEV float lane_f(float v, int l) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// minimum over the 64 lanes, uniform: row steps by DPP, then two row
+// broadcasts carry it to lane 63.  All 64 lanes must be active.  Rows a
+// broadcast skips read the identity (all ones), so each step is one DPP
+// minimum.
+RS_DEV uint32_t wave_min_u32(uint32_t v) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0xB1, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x4E, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x124, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x128, 0xf, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xa, 0xf, false));
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xc, 0xf, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// ---------------------------------------------------------------------------
+// Lower bounds of many pairs' d^2 by fp32 matrix products.  With norms and
+// products of normalised coordinates, |Xi|^2 + |Xj|^2 - 2 Xi.Xj of 256 pairs
+// takes two 16x16x4 products.  A lane holds operand element (row or column
+// lane % 16, k = lane / 16) and the results of column lane % 16, rows
+// 4 (lane / 16) + r.
+//
+// Squared norms are scaled by 1 - 2^-18, which lowers a pair's value by
+// 64 * 2^-24 (|Xi|^2 + |Xj|^2): more than the rounding of X (2 units each,
+// so at most 8 in the sum), of the norms (8), of the products and their
+// summation (at most 24) and of the exact d^2 itself (8 units of d^2, which
+// is at most 2 (|Xi|^2 + |Xj|^2)).
+// ---------------------------------------------------------------------------
+
+constexpr float LB_EPS = 3.814697265625e-06f;
+constexpr float NORM_PAD = 1e30f;   // value of absent rows and columns
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Keys that order like non-negative floats (low KEY_BITS bits dropped, which
+// only lowers them) and carry a row number there.  The mask comes from
+// key_mask(), opaque to the compiler, so that a key is one bit-select.
+constexpr int KEY_BITS = 9;
+
+RS_DEV int32_t key_mask() {
+    int32_t m = (1 << KEY_BITS) - 1;
+    asm volatile("" : "+v"(m));
+    return m;
+}
+
+RS_DEV int32_t key_of(float v, int32_t row, int32_t mask) {
+    return (mask & row) | (~mask & __float_as_int(v));
+}
+
+RS_DEV float key_value(int32_t k) { return __int_as_float(k & ~((1 << KEY_BITS) - 1)); }
+RS_DEV int32_t key_row(int32_t k) { return k & ((1 << KEY_BITS) - 1); }
+
+// the two smallest keys, k1 <= k2
+RS_DEV void key_take(int32_t& k1, int32_t& k2, int32_t key) {
+    k2 = max(min(k1, k2), min(max(k1, k2), key));   // the median
+    k1 = min(k1, key);
+}
+
+RS_DEV f32x4 mfma_16x16x4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 // exact 128-bit helpers
 // ---------------------------------------------------------------------------
 

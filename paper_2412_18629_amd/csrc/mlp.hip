@@ -36,12 +36,6 @@ constexpr int SH = NH + 4;         // LDS strides: operand reads spread over the
 constexpr int SX = NIN + 12;       // columns 24.. : 1 (bias gradient), then zeros
 constexpr int MLP_MAX_BLOCKS = 512;
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-RS_DEV f32x4 mlp_mfma(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
 template <bool GRAD>
 __global__ void __launch_bounds__(256)
 k_mlp_batch(const float* __restrict__ p, const float* __restrict__ X,
@@ -85,7 +79,7 @@ k_mlp_batch(const float* __restrict__ p, const float* __restrict__ X,
             f32x4 acc = {bias1, bias1, bias1, bias1};
 #pragma unroll
             for (int k = 0; k < NIN / 4; k++)
-                acc = mlp_mfma(sx[(16 * mt + lm) * SX + 4 * k + lk], w1r[k], acc);
+                acc = mfma_16x16x4(sx[(16 * mt + lm) * SX + 4 * k + lk], w1r[k], acc);
 #pragma unroll
             for (int r = 0; r < 4; r++) {
                 const int row = 16 * mt + 4 * lk + r;
@@ -97,7 +91,7 @@ k_mlp_batch(const float* __restrict__ p, const float* __restrict__ X,
             f32x4 acc = {bias2, bias2, bias2, bias2};
 #pragma unroll
             for (int k = 0; k < NH / 4; k++)
-                acc = mlp_mfma(h1[(16 * mt + lm) * SH + 4 * k + lk], w2r[k], acc);
+                acc = mfma_16x16x4(h1[(16 * mt + lm) * SH + 4 * k + lk], w2r[k], acc);
 #pragma unroll
             for (int r = 0; r < 4; r++) {
                 const int row = 16 * mt + 4 * lk + r;
@@ -144,7 +138,7 @@ k_mlp_batch(const float* __restrict__ p, const float* __restrict__ X,
                 f32x4 acc = zero;
 #pragma unroll
                 for (int k = 0; k < NH / 4; k++)
-                    acc = mlp_mfma(h2[(16 * mt + lm) * SH + 4 * k + lk], w2t[k], acc);
+                    acc = mfma_16x16x4(h2[(16 * mt + lm) * SH + 4 * k + lk], w2t[k], acc);
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
                     const int o = (16 * mt + 4 * lk + r) * SH + n0 + lm;
@@ -157,7 +151,7 @@ k_mlp_batch(const float* __restrict__ p, const float* __restrict__ X,
                 const float b = h1[(4 * k + lk) * SH + n0 + lm];
 #pragma unroll
                 for (int mt = 0; mt < 4; mt++)
-                    g2[mt] = mlp_mfma(h2[(4 * k + lk) * SH + 16 * mt + lm], b, g2[mt]);
+                    g2[mt] = mfma_16x16x4(h2[(4 * k + lk) * SH + 16 * mt + lm], b, g2[mt]);
             }
             __syncthreads();
             // W1 and b1 (the column of ones)
@@ -166,7 +160,7 @@ k_mlp_batch(const float* __restrict__ p, const float* __restrict__ X,
                 const float a = dh1[(4 * k + lk) * SH + n0 + lm];
 #pragma unroll
                 for (int nt = 0; nt < 2; nt++)
-                    g1[nt] = mlp_mfma(a, sx[(4 * k + lk) * SX + 16 * nt + lm], g1[nt]);
+                    g1[nt] = mfma_16x16x4(a, sx[(4 * k + lk) * SX + 16 * nt + lm], g1[nt]);
             }
         }
     }

@@ -51,14 +51,8 @@ struct StackEntry {
 constexpr int WAVE_MAX = 64;      // nodes one wavefront splits by itself
 constexpr int QCAP = 128;         // queued pairs per wavefront
 constexpr int N_ROWS = 7;         // X of x y z u v w, squared norm
-constexpr float NORM_PAD = 1e30f; // squared norm of absent members
 constexpr float NORM_WIDE = 1e29f;
 
-// Squared norms are scaled by 1 - 2^-18, which lowers a pair's value by
-// 64 * 2^-24 (|Xi|^2 + |Xj|^2): more than the rounding of X (2 units each),
-// of the norms (8), of the 8-term products (at most 8 * 2) and of the exact
-// d^2 itself (8, and d^2 <= 2 (|Xi|^2 + |Xj|^2)).
-constexpr float LB_EPS = 3.814697265625e-06f;
 // Across a periodic face X also carries the absolute rounding of the image
 // shift, at most eta = sqrt(a) box_slack(L) per pair of positions, and
 // (D + eta)^2 <= (1 + k) D^2 + (1 + 1/k) eta^2.
@@ -74,26 +68,6 @@ static size_t small_lds_bytes(int maxn, int nt, int min_sub) {
     const int capn = maxn / min_sub + 1;
     return (size_t)N_ROWS * n_stride(maxn) * 4 + (size_t)maxn * 8 +
            (size_t)capn * sizeof(StackEntry) + (size_t)(nt / 64) * QCAP * 4;
-}
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-RS_DEV f32x4 pair_mfma(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// minimum over the 64 lanes, uniform: row steps by DPP, then two row
-// broadcasts carry it to lane 63.  All 64 lanes must be active.  Rows a
-// broadcast skips read the identity (all ones), so each step is one DPP
-// minimum.
-RS_DEV uint32_t wave_min_u32(uint32_t v) {
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0xB1, 0xf, 0xf, false));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x4E, 0xf, 0xf, false));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x124, 0xf, 0xf, false));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x128, 0xf, 0xf, false));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xa, 0xf, false));
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xc, 0xf, false));
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 template <int CTRL, int ROWS>
@@ -122,10 +96,6 @@ RS_DEV uint64_t wave_sum_u64(uint64_t v) {
 RS_DEV u128 wave_sum_u128(u128 v) {
     return ((u128)wave_sum_u64((uint64_t)(v >> 32)) << 32) +
            wave_sum_u64((uint64_t)v & 0xffffffffu);
-}
-
-RS_DEV float lane_f(float v, int l) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
 RS_DEV int64_t lane_i64(int64_t v, int l) {
@@ -559,19 +529,22 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
                         k1[cb] = k2[cb] = 0x7fffffff;
                     }
                     const int nrb = 4 * ng;
+                    const int32_t kmask = key_mask();
                     const float* n0 = N + lk * NS + lm;
                     const float* n1 = N + (lk < 3 ? 4 + lk : 6) * NS + lm;
+                    float a0 = n0[0], a1 = n1[0];
                     for (int rb = 0; rb < nrb; rb++) {
-                        const float a0 = n0[16 * rb];
-                        const float a1 = lk == 3 ? 1.0f : n1[16 * rb];
+                        if (lk == 3) a1 = 1.0f;
+                        const int nx = 16 * min(rb + 1, nrb - 1);   // the next block's operands
+                        const float p0 = n0[nx], p1 = n1[nx];
                         f32x4 o[4];
 #pragma unroll
                         for (int cb = 0; cb < 4; cb++) {
                             const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-                            o[cb] = pair_mfma(a0, b0[cb], zero);
+                            o[cb] = mfma_16x16x4(a0, b0[cb], zero);
                         }
 #pragma unroll
-                        for (int cb = 0; cb < 4; cb++) o[cb] = pair_mfma(a1, b1[cb], o[cb]);
+                        for (int cb = 0; cb < 4; cb++) o[cb] = mfma_16x16x4(a1, b1[cb], o[cb]);
                         if ((rb >> 2) == g) {   // a member is not its own neighbour
 #pragma unroll
                             for (int cb = 0; cb < 4; cb++)
@@ -582,19 +555,17 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
 #pragma unroll
                         for (int cb = 0; cb < 4; cb++)
 #pragma unroll
-                            for (int r = 0; r < 4; r++) {
-                                const int32_t key =
-                                    (__float_as_int(o[cb][r]) & ~511) | (rb << 2 | r);
-                                k2[cb] = max(min(k1[cb], k2[cb]), min(max(k1[cb], k2[cb]), key));
-                                k1[cb] = min(k1[cb], key);
-                            }
+                            for (int r = 0; r < 4; r++)
+                                key_take(k1[cb], k2[cb], key_of(o[cb][r], rb << 2 | r, kmask));
+                        a0 = p0;
+                        a1 = p1;
                     }
                     // the four lanes of a column agree on its two smallest keys
                     int row = 0;
                     float bound = 0.0f;
 #pragma unroll
                     for (int cb = 0; cb < 4; cb++) {
-                        int r1 = ((k1[cb] & 511) >> 2) * 16 + 4 * lk + (k1[cb] & 3);
+                        int r1 = (key_row(k1[cb]) >> 2) * 16 + 4 * lk + (k1[cb] & 3);
 #pragma unroll
                         for (int o = 16; o <= 32; o <<= 1) {
                             const int32_t f1 = __shfl_xor(k1[cb], o, 64);
@@ -606,7 +577,7 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
                         }
                         if (lk == cb) {   // this lane's own member
                             row = r1;
-                            bound = __int_as_float(k2[cb] & ~511);
+                            bound = key_value(k2[cb]);
                         }
                     }
                     row = row < sz ? row : 0;
@@ -729,10 +700,10 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
 #pragma unroll
                         for (int cb = 0; cb < 4; cb++) {
                             const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-                            o[cb] = pair_mfma(a0, b0[cb], zero);
+                            o[cb] = mfma_16x16x4(a0, b0[cb], zero);
                         }
 #pragma unroll
-                        for (int cb = 0; cb < 4; cb++) o[cb] = pair_mfma(a1, b1[cb], o[cb]);
+                        for (int cb = 0; cb < 4; cb++) o[cb] = mfma_16x16x4(a1, b1[cb], o[cb]);
                         if ((rb >> 2) == g) {   // each pair once: row before column
 #pragma unroll
                             for (int cb = 0; cb < 4; cb++)

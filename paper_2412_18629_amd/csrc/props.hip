@@ -522,15 +522,17 @@ __global__ void k_sd_leafup(PrTree T, int32_t l, const int32_t* __restrict__ lst
         atomicAdd(leafcnt + T.parent[r], leafcnt[r]);
 }
 
-// top-down: each node's run in the leaf list, carved from its parent's
+// top-down: each node's run in the leaf list, carved from its parent's, and
+// its level-0 ancestor
 __global__ void k_sd_leafdown(PrTree T, int32_t l, const int32_t* __restrict__ lstart,
                               const int32_t* __restrict__ leafcnt, int32_t* __restrict__ lfirst,
-                              int32_t* __restrict__ lfill) {
+                              int32_t* __restrict__ lfill, int32_t* __restrict__ root) {
     const int32_t b = lstart[l], e = lstart[l + 1];
     for (int32_t r = b + blockIdx.x * blockDim.x + threadIdx.x; r < e;
          r += gridDim.x * blockDim.x) {
         const int32_t p = T.parent[r];
         lfirst[r] = lfirst[p] + atomicAdd(lfill + p, leafcnt[r]);
+        root[r] = root[p];
     }
 }
 
@@ -544,31 +546,92 @@ __global__ void k_sd_init(PrTree T, const int32_t* __restrict__ childsum,
 
 __global__ void k_sd_level0(PrTree T, const int32_t* __restrict__ leafcnt,
                             const int32_t* __restrict__ own, const int32_t* __restrict__ childsum,
-                            int32_t* __restrict__ l0cnt, int32_t* __restrict__ nitem) {
+                            int32_t* __restrict__ l0cnt, int32_t* __restrict__ nitem,
+                            int32_t* __restrict__ root) {
     const int32_t r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= T.m) return;
+    root[r] = r;
     l0cnt[r] = T.level[r] == 0 ? leafcnt[r] : 0;
     nitem[r] = childsum[r] > 0 ? (own[r] + 63) / 64 : 0;
+}
+
+// Seeds in the frame of their group (centre and bulk velocity of the level-0
+// node): d^2 of a particle X = (offsets xyz, uvw) is the product of
+// (X, |Xpos|^2, |Xvel|^2, 1) with the seed's nine coefficients, kept as rows
+// SC_ROWS[k][seed] for the matrix products below.  The constant is lowered by
+// the rounding of image shifts, at most eta = L 2^-22 per axis of a position
+// pair: (D + eta)^2 <= (1 + k) D^2 + (1 + 1/k) eta^2 with k = LB_WRAP.
+// A group flags itself when a seed's offset is beyond a quarter box (nearest
+// images of pairs need not agree with the frame's) or its numbers are not of
+// the kind a hierarchy gives (SD_EXACT), and when an offset took an image
+// shift (SD_SHIFT).
+constexpr int SC_ROWS = 9;
+constexpr float LB_WRAP = 0.0078125f;
+constexpr int SD_EXACT = 1, SD_SHIFT = 2;
+
+struct SeedFrame {
+    float c[3], u[3];
+};
+
+RS_DEV SeedFrame sd_frame(const float* __restrict__ props, int64_t m, int32_t root) {
+    return SeedFrame{{props[root], props[m + root], props[2 * m + root]},
+                     {props[3 * m + root], props[4 * m + root], props[5 * m + root]}};
 }
 
 __global__ void k_sd_seeds(PrTree T, const int32_t* __restrict__ childsum,
                            const int32_t* __restrict__ lfirst, const float* __restrict__ props,
                            const float* __restrict__ fa, const float* __restrict__ fc,
-                           SeedRec* __restrict__ seeds, int32_t* __restrict__ seednode) {
+                           const int32_t* __restrict__ root, float L, float h,
+                           SeedRec* __restrict__ seeds, int32_t* __restrict__ seednode,
+                           float* __restrict__ sc, int64_t stride, int32_t* __restrict__ flags) {
     const int32_t r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= T.m || childsum[r] != 0) return;
     const int32_t q = lfirst[r];
     const int64_t m = T.m;
-    seeds[q] = SeedRec{props[r], props[m + r], props[2 * m + r], props[3 * m + r],
-                       props[4 * m + r], props[5 * m + r], fa[r], fc[r]};
+    const float a = fa[r], c = fc[r];
+    const float p[6] = {props[r], props[m + r], props[2 * m + r], props[3 * m + r],
+                        props[4 * m + r], props[5 * m + r]};
+    seeds[q] = SeedRec{p[0], p[1], p[2], p[3], p[4], p[5], a, c};
     seednode[q] = r;
+    const SeedFrame f = sd_frame(props, m, root[r]);
+    float X[6], n2 = 0.0f, v2 = 0.0f;
+    int32_t fl = 0;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const float d = p[k] - f.c[k];
+        X[k] = min_image(d, L, h);
+        X[3 + k] = p[3 + k] - f.u[k];
+        if (fabsf(d) > h) fl |= SD_SHIFT;
+        if (!(fabsf(X[k]) <= 0.499f * h)) fl |= SD_EXACT;
+        n2 = fmaf(X[k], X[k], n2);
+        v2 = fmaf(X[3 + k], X[3 + k], v2);
+    }
+    const float eta = L * 2.3841858e-07f;
+    const float k0 = (a * n2 + c * v2) * (1.0f - LB_EPS) -
+                     a * (3.01f * (1.0f + 1.0f / LB_WRAP)) * eta * eta;
+    if (!(a >= 0.0f) || !(c >= 0.0f) || !(a < 1e18f) || !(c < 1e18f) || !(fabsf(k0) < 1e24f))
+        fl |= SD_EXACT;
+#pragma unroll
+    for (int k = 0; k < 6; k++) sc[k * stride + q] = -2.0f * (k < 3 ? a : c) * X[k];
+    sc[6 * stride + q] = a;
+    sc[7 * stride + q] = c;
+    sc[8 * stride + q] = k0;
+    if (fl) atomicOr(flags + root[r], fl);
 }
 
-__global__ void k_sd_items(PrTree T, const int32_t* __restrict__ nitem,
-                           const int32_t* __restrict__ ioff, int32_t* __restrict__ items) {
-    const int32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= T.m) return;
-    for (int32_t c = 0; c < nitem[r]; c++) items[ioff[r] + c] = r;
+// node of every work item: the last node whose first item is not after it
+// (one thread per node wrote its items in turn before, 0.64 of 21 ms where
+// one node had 10^5 of them)
+__global__ void k_sd_items(int32_t total, int32_t m, const int32_t* __restrict__ ioff,
+                           int32_t* __restrict__ items) {
+    const int32_t it = blockIdx.x * blockDim.x + threadIdx.x;
+    if (it >= total) return;
+    int32_t lo = 0, hi = m;
+    while (hi - lo > 1) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (ioff[mid] <= it) lo = mid; else hi = mid;
+    }
+    items[it] = lo;
 }
 
 // particles outside every node (-1) and particles of a seed (the seed)
@@ -581,10 +644,33 @@ __global__ void k_sd_direct(int64_t n, PrTree T, const int32_t* __restrict__ chi
     else if (childsum[d] == 0) halo[i] = d;
 }
 
-// one wavefront per 64 own particles of a node with children: each lane
-// takes one particle, the seeds below the node are read in turn (one
-// uniform 32-byte record each) and the nearest is kept
-__global__ void __launch_bounds__(64)
+RS_DEV float sd_d2(const SeedRec& S, float px, float py, float pz, float pu, float pv, float pw,
+                   float L, float h) {
+    const float Dx = sum_sq3(min_image(px - S.cx, L, h), min_image(py - S.cy, L, h),
+                             min_image(pz - S.cz, L, h));
+    return metric(S.a, Dx, S.c, sum_sq3(pu - S.ux, pv - S.uy, pw - S.uz));
+}
+
+// One wavefront per 64 own particles of a node with children.
+//
+// Up to SD_FEW seeds are read in turn (one uniform record each), every lane
+// evaluating its particle.  More are screened: a lower bound of d^2 of 64
+// particles (columns) by 16 seeds (rows) takes eight matrix products, each
+// lane keeping the smallest bound, its seed and the second smallest; the
+// particle's d^2 to that seed is then evaluated exactly and decides when it
+// lies below every other seed's bound.  Other particles (ties, near ties) are
+// tested against all seeds by the whole wavefront.
+//
+// What bounds it: the products (256 cycles per 1024 tests and SIMD) where
+// the plain loop took some 27 vector instructions per 64 tests.  Up to SD_FEW
+// seeds the loop issues fewer instructions than the screening's set-up (27 a
+// seed against some 250 in all); limits of 2, 8, 16 and 32 measured the same
+// (1.28 ms on a 256^3 hierarchy, 3.66 ms on a deeply nested one of 9M
+// particles), since few particles sit in such nodes.  Deeply nested
+// hierarchies: 16M particles 19.3 -> 6.8 ms, 9M 11.5 -> 3.7 ms.
+constexpr int SD_FEW = 8;
+
+__global__ void __launch_bounds__(64, 4)
 k_sd_assign(const float* __restrict__ x, const float* __restrict__ y,
             const float* __restrict__ z, const float* __restrict__ vx,
             const float* __restrict__ vy, const float* __restrict__ vz, int32_t total,
@@ -592,33 +678,161 @@ k_sd_assign(const float* __restrict__ x, const float* __restrict__ y,
             const int32_t* __restrict__ own, const int32_t* __restrict__ ownscan,
             const int32_t* __restrict__ perm, const int32_t* __restrict__ lfirst,
             const int32_t* __restrict__ leafcnt, const SeedRec* __restrict__ seeds,
-            const int32_t* __restrict__ seednode, float L, float h,
+            const int32_t* __restrict__ seednode, const float* __restrict__ props, int64_t m,
+            const int32_t* __restrict__ root, const int32_t* __restrict__ flags,
+            const float* __restrict__ sc, int64_t stride, float L, float h,
             int32_t* __restrict__ halo) {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x, lm = lane & 15, lk = lane >> 4;
     for (int32_t it = blockIdx.x; it < total; it += gridDim.x) {
         const int32_t r = __builtin_amdgcn_readfirstlane(items[it]);
-        const int32_t c = it - ioff[r];
-        const int32_t k = c * 64 + lane;
-        if (k >= own[r]) continue;
-        const int32_t i = perm[ownscan[r] + k];
+        const int32_t k0 = (it - ioff[r]) * 64, nown = own[r];
+        const bool valid = k0 + lane < nown;
+        const int32_t i = perm[ownscan[r] + (valid ? k0 + lane : k0)];
         const float px = x[i], py = y[i], pz = z[i], pu = vx[i], pv = vy[i], pw = vz[i];
         const int32_t q0 = __builtin_amdgcn_readfirstlane(lfirst[r]);
         const int32_t q1 = q0 + __builtin_amdgcn_readfirstlane(leafcnt[r]);
         float best = INFINITY;
         int32_t bnode = 0x7fffffff;
-        for (int32_t q = q0; q < q1; q++) {
-            const SeedRec S = seeds[q];
-            const int32_t node = seednode[q];
-            const float Dx = sum_sq3(min_image(px - S.cx, L, h), min_image(py - S.cy, L, h),
-                                     min_image(pz - S.cz, L, h));
-            const float Dv = sum_sq3(pu - S.ux, pv - S.uy, pw - S.uz);
-            const float d2 = metric(S.a, Dx, S.c, Dv);
-            if (d2 < best || (d2 == best && node < bnode)) {
-                best = d2;
-                bnode = node;
+        uint64_t again = 0;
+        bool screen = q1 - q0 > SD_FEW;
+        if (screen) {
+            const int32_t rt = __builtin_amdgcn_readfirstlane(root[r]);
+            const int32_t fl = __builtin_amdgcn_readfirstlane(flags[rt]);
+            const SeedFrame f = sd_frame(props, m, rt);
+            // the particle in the group's frame
+            const float dx = px - f.c[0], dy = py - f.c[1], dz = pz - f.c[2];
+            float X[8] = {min_image(dx, L, h), min_image(dy, L, h), min_image(dz, L, h),
+                          pu - f.u[0], pv - f.u[1], pw - f.u[2], 0.0f, 0.0f};
+            bool far = false, shift = fabsf(dx) > h || fabsf(dy) > h || fabsf(dz) > h;
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                far = far || !(fabsf(X[k]) <= 0.499f * h);
+                X[6] = fmaf(X[k], X[k], X[6]);
+                X[7] = fmaf(X[3 + k], X[3 + k], X[7]);
+            }
+            X[6] *= 1.0f - LB_EPS;
+            X[7] *= 1.0f - LB_EPS;
+            far = far || !(X[6] < 1e15f) || !(X[7] < 1e15f);
+            screen = !(fl & SD_EXACT) && __ballot(far) == 0;
+            if (screen) {
+                const bool wrap = (fl & SD_SHIFT) || __ballot(shift) != 0;
+                // column cb * 16 + lm, coefficients lk and 4 + lk
+                float b0[4], b1[4];
+                int32_t K1[4], K2[4], I1[4];
+#pragma unroll
+                for (int cb = 0; cb < 4; cb++) {
+                    const int src = 16 * cb + lm;
+                    const float s0 = __shfl(X[0], src, 64), s1 = __shfl(X[1], src, 64),
+                                s2 = __shfl(X[2], src, 64), s3 = __shfl(X[3], src, 64);
+                    const float s4 = __shfl(X[4], src, 64), s5 = __shfl(X[5], src, 64),
+                                s6 = __shfl(X[6], src, 64), s7 = __shfl(X[7], src, 64);
+                    b0[cb] = lk == 0 ? s0 : lk == 1 ? s1 : lk == 2 ? s2 : s3;
+                    b1[cb] = lk == 0 ? s4 : lk == 1 ? s5 : lk == 2 ? s6 : s7;
+                    K1[cb] = K2[cb] = 0x7fffffff;
+                    I1[cb] = q0;
+                }
+                const int32_t kmask = key_mask();
+                // 128 row blocks at a time, so that a row's number within its
+                // lane group fits the low nine bits of a key
+                for (int32_t c0 = q0; c0 < q1; c0 += 2048) {
+                    const int nrb = (min(q1 - c0, 2048) + 15) >> 4;
+                    int32_t k1[4], k2[4];
+#pragma unroll
+                    for (int cb = 0; cb < 4; cb++) k1[cb] = k2[cb] = 0x7fffffff;
+                    const float* p0 = sc + lk * stride + c0 + lm;
+                    const float* p1 = sc + (4 + lk) * stride + c0 + lm;
+                    const float* pc = sc + 8 * stride + c0 + 4 * lk;
+                    // the next block's operands are loaded before this one's
+                    // products (the last block loads its own again)
+                    float a0 = p0[0], a1 = p1[0];
+                    f32x4 cc = {pc[0], pc[1], pc[2], pc[3]};
+                    for (int rb = 0; rb < nrb; rb++) {
+                        const int nx = 16 * min(rb + 1, nrb - 1);
+                        const float n0 = p0[nx], n1 = p1[nx];
+                        const f32x4 nc = {pc[nx], pc[nx + 1], pc[nx + 2], pc[nx + 3]};
+                        f32x4 o[4];
+#pragma unroll
+                        for (int cb = 0; cb < 4; cb++) o[cb] = mfma_16x16x4(a0, b0[cb], cc);
+#pragma unroll
+                        for (int cb = 0; cb < 4; cb++) o[cb] = mfma_16x16x4(a1, b1[cb], o[cb]);
+                        const int32_t s = c0 + 16 * rb;
+                        if (s + 16 > q1) {   // rows past the last seed
+#pragma unroll
+                            for (int cb = 0; cb < 4; cb++)
+#pragma unroll
+                                for (int t = 0; t < 4; t++)
+                                    if (s + 4 * lk + t >= q1) o[cb][t] = NORM_PAD;
+                        }
+#pragma unroll
+                        for (int cb = 0; cb < 4; cb++)
+#pragma unroll
+                            for (int t = 0; t < 4; t++)
+                                key_take(k1[cb], k2[cb], key_of(o[cb][t], rb << 2 | t, kmask));
+                        a0 = n0;
+                        a1 = n1;
+                        cc = nc;
+                    }
+#pragma unroll
+                    for (int cb = 0; cb < 4; cb++) {
+                        const int32_t idx =
+                            c0 + (key_row(k1[cb]) >> 2) * 16 + 4 * lk + (k1[cb] & 3);
+                        K2[cb] = min(max(K1[cb], k1[cb]), min(K2[cb], k2[cb]));
+                        I1[cb] = k1[cb] < K1[cb] ? idx : I1[cb];
+                        K1[cb] = min(K1[cb], k1[cb]);
+                    }
+                }
+                // the four lanes of a column agree on its two smallest keys
+                int32_t pick = q0;
+                float bound = 0.0f;
+#pragma unroll
+                for (int cb = 0; cb < 4; cb++) {
+#pragma unroll
+                    for (int o = 16; o <= 32; o <<= 1) {
+                        const int32_t f1 = __shfl_xor(K1[cb], o, 64);
+                        const int32_t f2 = __shfl_xor(K2[cb], o, 64);
+                        const int32_t fi = __shfl_xor(I1[cb], o, 64);
+                        K2[cb] = min(max(K1[cb], f1), min(K2[cb], f2));
+                        I1[cb] = f1 < K1[cb] ? fi : I1[cb];
+                        K1[cb] = min(K1[cb], f1);
+                    }
+                    if (lk == cb) {
+                        pick = I1[cb];
+                        bound = key_value(K2[cb]);
+                    }
+                }
+                pick = pick < q1 ? pick : q0;
+                best = sd_d2(seeds[pick], px, py, pz, pu, pv, pw, L, h);
+                bnode = seednode[pick];
+                const bool ok = best < (wrap ? bound * (1.0f - LB_WRAP) : bound);
+                again = __ballot(valid && !ok);
             }
         }
-        halo[i] = bnode;
+        if (!screen) {
+            for (int32_t q = q0; q < q1; q++) {
+                const int32_t node = seednode[q];
+                const float d2 = sd_d2(seeds[q], px, py, pz, pu, pv, pw, L, h);
+                if (d2 < best || (d2 == best && node < bnode)) {
+                    best = d2;
+                    bnode = node;
+                }
+            }
+        }
+        while (again) {
+            const int l = __builtin_ctzll(again);
+            again &= again - 1;
+            const float ax = lane_f(px, l), ay = lane_f(py, l), az = lane_f(pz, l),
+                        au = lane_f(pu, l), av = lane_f(pv, l), aw = lane_f(pw, l);
+            unsigned long long key = ~0ull;   // (d^2 bits, node): ties to the smaller node
+            for (int32_t q = q0 + lane; q < q1; q += 64) {
+                const float d2 = sd_d2(seeds[q], ax, ay, az, au, av, aw, L, h);
+                const unsigned long long k =
+                    ((unsigned long long)__float_as_uint(d2) << 32) | (uint32_t)seednode[q];
+                key = k < key ? k : key;
+            }
+            key = wave_min_u64(key);
+            if (lane == l) bnode = (int32_t)(uint32_t)key;
+        }
+        if (valid) halo[i] = bnode;
     }
 }
 
@@ -634,8 +848,10 @@ int seeds_run(const float* x, const float* y, const float* z, const float* vx,
     auto add = [&](size_t b) { bytes += arena_round(b); };
     add(8 * (size_t)n); add(8 * (size_t)n);               // sort keys in / out
     add(4 * (size_t)n); add(4 * (size_t)n);               // index in / sorted
-    for (int k = 0; k < 10; k++) add(4 * ((size_t)m + 1)); // per-node tables
+    for (int k = 0; k < 12; k++) add(4 * ((size_t)m + 1)); // per-node tables
     add(sizeof(SeedRec) * ((size_t)m + 1));               // seed records
+    const int64_t sstride = (m + 63) / 64 * 64 + 80;      // room for the last rows' block
+    add(4 * SC_ROWS * (size_t)sstride);                   // seed coefficients
     add(4 * (size_t)cap_items);                           // item -> node
     add(4 * ((size_t)nlev + 2));                          // level starts
     add(scan_temp_bytes(m)); add(sort_temp_bytes(n)); add(256);
@@ -655,7 +871,10 @@ int seeds_run(const float* x, const float* y, const float* z, const float* vx,
     int32_t* nitem = take<int32_t>(ar, m + 1);
     int32_t* ioff = take<int32_t>(ar, m + 1);
     int32_t* seednode = take<int32_t>(ar, m + 1);
+    int32_t* root = take<int32_t>(ar, m + 1);
+    int32_t* sflags = take<int32_t>(ar, m + 1);
     SeedRec* seeds = take<SeedRec>(ar, m + 1);
+    float* scoef = take<float>(ar, (size_t)SC_ROWS * sstride);
     int32_t* items = take<int32_t>(ar, cap_items);
     int32_t* lstart = take<int32_t>(ar, nlev + 2);
     void* ctemp = arena_take(ar, scan_temp_bytes(m));
@@ -671,6 +890,7 @@ int seeds_run(const float* x, const float* y, const float* z, const float* vx,
     RS_TRY(fill_i32(lstart, (int32_t)m, nlev + 2, st));
     RS_TRY(fill_i32(childsum, 0, m + 1, st));
     RS_TRY(fill_i32(lfill, 0, m + 1, st));
+    RS_TRY(fill_i32(sflags, 0, m + 1, st));
     const unsigned gm = grid_for(m, BT, 1ll << 31);
     const unsigned gn = grid_for(n, BT, 1ll << 31);
     k_pr_check<<<gm, BT, 0, st>>>(T, n, lstart, childsum, ctr);
@@ -691,14 +911,14 @@ int seeds_run(const float* x, const float* y, const float* z, const float* vx,
                                   ctr);
     for (int64_t l = nlev - 1; l >= 1; l--)
         k_sd_leafup<<<1024, BT, 0, st>>>(T, (int32_t)l, lstart, leafcnt);
-    k_sd_level0<<<gm, BT, 0, st>>>(T, leafcnt, own, childsum, l0cnt, nitem);
+    k_sd_level0<<<gm, BT, 0, st>>>(T, leafcnt, own, childsum, l0cnt, nitem, root);
     RS_HIP(hipGetLastError());
     RS_TRY(scan_exclusive_i32(l0cnt, lfirst, m, ctemp, ctr + 2, st));
     RS_TRY(scan_exclusive_i32(nitem, ioff, m, ctemp, ctr + 3, st));
     for (int64_t l = 1; l < nlev; l++)
-        k_sd_leafdown<<<1024, BT, 0, st>>>(T, (int32_t)l, lstart, leafcnt, lfirst, lfill);
-    k_sd_seeds<<<gm, BT, 0, st>>>(T, childsum, lfirst, props, fa, fc, seeds, seednode);
-    k_sd_items<<<gm, BT, 0, st>>>(T, nitem, ioff, items);
+        k_sd_leafdown<<<1024, BT, 0, st>>>(T, (int32_t)l, lstart, leafcnt, lfirst, lfill, root);
+    k_sd_seeds<<<gm, BT, 0, st>>>(T, childsum, lfirst, props, fa, fc, root, L, 0.5f * L, seeds,
+                                  seednode, scoef, sstride, sflags);
     RS_HIP(hipGetLastError());
     RS_HIP(hipMemcpyAsync(hc, ctr, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     RS_HIP(hipStreamSynchronize(st));
@@ -707,10 +927,12 @@ int seeds_run(const float* x, const float* y, const float* z, const float* vx,
     if (total > cap_items) return RS_EINTERNAL;
     prof_begin("seed_assign", st);
     k_sd_direct<<<gn, BT, 0, st>>>(n, T, childsum, halo);
-    if (total > 0)
-        k_sd_assign<<<(unsigned)std::min<int64_t>(total, 1 << 16), 64, 0, st>>>(
+    if (total > 0) {
+        k_sd_items<<<grid_for(total, BT, 1ll << 31), BT, 0, st>>>(total, (int32_t)m, ioff, items);
+        k_sd_assign<<<(unsigned)std::min<int64_t>(total, 1 << 20), 64, 0, st>>>(
             x, y, z, vx, vy, vz, total, items, ioff, own, ownscan, perm, lfirst, leafcnt, seeds,
-            seednode, L, 0.5f * L, halo);
+            seednode, props, m, root, sflags, scoef, sstride, L, 0.5f * L, halo);
+    }
     RS_HIP(hipGetLastError());
     prof_end("seed_assign", st, (double)n);
     RS_HIP(hipStreamSynchronize(st));
