@@ -124,6 +124,22 @@ RS_DEV unsigned long long wave_min_u64(unsigned long long v) {
     return v;
 }
 
+// Workgroups are dispatched round-robin over the 8 XCDs, each with its own
+// L2.  Blocks are remapped so that every XCD runs consecutive chunks of C
+// tiles: neighbouring tiles, which read mostly the same candidate data, then
+// share one L2.  The grid is rounded up to whole rounds of 8*C blocks; the
+// mapping is a bijection on the rounded range, and blocks whose tile index
+// is past the end exit.
+constexpr int XCDS = 8;
+RS_DEV int xcd_chunk_index(int b, int C) {
+    const int x = b % XCDS, r = b / XCDS;
+    return ((r / C) * XCDS + x) * C + r % C;
+}
+inline int xcd_chunk_grid(int n, int C) {
+    const int g = XCDS * C;
+    return (n + g - 1) / g * g;
+}
+
 // value of lane l (uniform) in every lane
 RS_DEV float lane_f(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));

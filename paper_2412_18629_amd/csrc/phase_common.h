@@ -151,21 +151,6 @@ int tree_build(TreeBuf& tb, int32_t* root, const uint64_t* skeys, const LNode* n
 int tree_refit_active(TreeBuf& tb, int32_t n_entry, const std::vector<int32_t>& level_begin,
                       const Members& T, const int32_t* mnode, const LParam* prm,
                       const PhaseParams& pp, const float* d2, hipStream_t st);
-// Workgroups are dispatched round-robin over the 8 XCDs, each with its own
-// L2.  Blocks are remapped so that every XCD runs consecutive chunks of C
-// tiles: neighbouring tiles, which read mostly the same candidate data, then
-// share one L2.  The grid is rounded up to whole rounds of 8*C blocks; the
-// mapping is a bijection on the rounded range, and blocks whose tile index
-// is past the end exit.
-constexpr int XCDS = 8;
-RS_DEV int xcd_chunk_index(int b, int C) {
-    const int x = b % XCDS, r = b / XCDS;
-    return ((r / C) * XCDS + x) * C + r % C;
-}
-inline int xcd_chunk_grid(int n, int C) {
-    const int g = XCDS * C;
-    return (n + g - 1) / g * g;
-}
 // chunk length: whole rounds stay at least 64 so the XCDs finish together;
 // the longest chunk comes from the tuning table
 inline int xcd_chunk(int ntiles) {
