@@ -18,7 +18,7 @@
 //              being linked already); octant pairs in the 27-cell
 //              neighbourhood are tested with early exit on the first linked
 //              pair and skipped when already in one component.  Pairs of
-//              more than HEAVY_PAIRS member pairs are queued and tested
+//              more than heavy_pairs member pairs are queued and tested
 //              afterwards, one wavefront per pair.  Without auto-link (grids
 //              of under three cells per axis, or octants too wide) the
 //              union-find runs over slots and every member pair is tested.
@@ -111,32 +111,138 @@ __global__ void k_gather3(const int32_t* __restrict__ perm, const float* __restr
     sz[s] = rec[3 * i + 2];
 }
 
-// run-start flags of octants and of cells in the sorted key order
-__global__ void k_run_flags(const uint64_t* __restrict__ keys, int64_t n,
-                            int32_t* __restrict__ oflag, int32_t* __restrict__ cflag) {
-    int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    uint64_t k = keys[s];
-    uint64_t p = s ? keys[s - 1] : ~0ull;
-    oflag[s] = (s == 0 || k != p) ? 1 : 0;
-    cflag[s] = (s == 0 || (k >> 3) != (p >> 3)) ? 1 : 0;
+// Occupied octants and cells are runs of equal keys in the sorted order.
+// Their numbers come from counts per tile of OT_TILE slots (k_oct_sums), the
+// scan of those by one workgroup (k_oct_scan), and a second reading of the
+// keys that numbers the runs inside the tile and writes the tables
+// (k_oct_tables): 28 bytes a slot in two passes, where run flags, their two
+// scans and the tables took 60 in seven.  A pair of counts is packed as
+// octants << 32 | cells.
+constexpr int OT_T = 256, OT_I = 8, OT_TILE = OT_T * OT_I;
+
+// does an octant (and a cell) start at slot s?
+RS_DEV void run_start(const uint64_t* __restrict__ keys, int64_t s, uint64_t k, bool& oct,
+                      bool& cell) {
+    const uint64_t p = s ? keys[s - 1] : ~0ull;
+    oct = s == 0 || k != p;
+    cell = s == 0 || (k >> 3) != (p >> 3);
 }
 
-__global__ void k_tables(const uint64_t* __restrict__ keys, int64_t n,
-                         const int32_t* __restrict__ oflag, const int32_t* __restrict__ oex,
-                         const int32_t* __restrict__ cflag, const int32_t* __restrict__ cex,
-                         int32_t* __restrict__ oct_start, uint8_t* __restrict__ oct_bits,
-                         int32_t* __restrict__ cell_oct, uint64_t* __restrict__ cell_key) {
-    int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    if (oflag[s]) {
-        int32_t o = oex[s];
-        oct_start[o] = (int32_t)s;
-        oct_bits[o] = (uint8_t)(keys[s] & 7);
-        if (cflag[s]) {
-            int32_t c = cex[s];
-            cell_oct[c] = o;
-            cell_key[c] = keys[s] >> 3;
+__global__ void __launch_bounds__(OT_T)
+k_oct_sums(const uint64_t* __restrict__ keys, int64_t n,
+           unsigned long long* __restrict__ sums) {
+    __shared__ unsigned long long part[OT_T / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * OT_TILE + w * (OT_I * 64) + lane;
+    unsigned long long c = 0;
+#pragma unroll
+    for (int r = 0; r < OT_I; r++) {
+        const int64_t s = base + r * 64;
+        bool oct = false, cell = false;
+        if (s < n) run_start(keys, s, keys[s], oct, cell);
+        c += ((unsigned long long)__popcll(__ballot(oct)) << 32) |
+             (unsigned long long)__popcll(__ballot(cell));
+    }
+    if (lane == 0) part[w] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
+}
+
+// exclusive scan in place; counts[0] = octants, counts[1] = cells in all
+constexpr int OS_T = 1024, OS_I = 4;
+
+__global__ void __launch_bounds__(OS_T)
+k_oct_scan(int64_t ntiles, unsigned long long* __restrict__ sums, int32_t* __restrict__ counts) {
+    __shared__ unsigned long long part[OS_T / 64];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    unsigned long long carry = 0;
+    for (int64_t b = 0; b < ntiles; b += OS_T * OS_I) {
+        const int64_t i0 = b + tid * OS_I;
+        unsigned long long v[OS_I], c = 0;
+#pragma unroll
+        for (int k = 0; k < OS_I; k++) {
+            v[k] = i0 + k < ntiles ? sums[i0 + k] : 0;
+            c += v[k];
+        }
+        unsigned long long inc = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long t = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += t;
+        }
+        if (lane == 63) part[w] = inc;
+        __syncthreads();
+        unsigned long long run = carry + inc - c;
+#pragma unroll
+        for (int q = 0; q < OS_T / 64; q++) {
+            if (q < w) run += part[q];
+            carry += part[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < OS_I; k++) {
+            if (i0 + k < ntiles) sums[i0 + k] = run;
+            run += v[k];
+        }
+    }
+    if (tid == 0) {
+        counts[0] = (int32_t)(carry >> 32);
+        counts[1] = (int32_t)(carry & 0xffffffffull);
+    }
+}
+
+// The tables, each slot's octant, and the auto-linked union-find's start:
+// every octant its own parent, its smallest original index that of its first
+// slot (the sort is stable).
+__global__ void __launch_bounds__(OT_T)
+k_oct_tables(const uint64_t* __restrict__ keys, int64_t n,
+             const unsigned long long* __restrict__ sums, const int32_t* __restrict__ perm,
+             int32_t* __restrict__ oct_start, uint8_t* __restrict__ oct_bits,
+             int32_t* __restrict__ cell_oct, uint64_t* __restrict__ cell_key,
+             int32_t* __restrict__ slot_oct, int32_t* __restrict__ poct,
+             int32_t* __restrict__ minidx) {
+    __shared__ unsigned long long part[OT_T / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * OT_TILE + w * (OT_I * 64) + lane;
+    uint64_t key[OT_I], om[OT_I], cm[OT_I];
+    unsigned long long c = 0;
+#pragma unroll
+    for (int r = 0; r < OT_I; r++) {
+        const int64_t s = base + r * 64;
+        bool oct = false, cell = false;
+        key[r] = s < n ? keys[s] : 0;
+        if (s < n) run_start(keys, s, key[r], oct, cell);
+        om[r] = __ballot(oct);
+        cm[r] = __ballot(cell);
+        c += ((unsigned long long)__popcll(om[r]) << 32) | (unsigned long long)__popcll(cm[r]);
+    }
+    if (lane == 0) part[w] = c;
+    __syncthreads();
+    unsigned long long run = sums[blockIdx.x];
+    for (int q = 0; q < w; q++) run += part[q];
+    int32_t o0 = (int32_t)(run >> 32), c0 = (int32_t)(run & 0xffffffffull);
+#pragma unroll
+    for (int r = 0; r < OT_I; r++) {
+        const int64_t s = base + r * 64;
+        const uint64_t upto = lanemask_lt() | (1ull << lane);
+        const int32_t o = o0 + __popcll(om[r] & upto) - 1, cl = c0 + __popcll(cm[r] & upto) - 1;
+        o0 += __popcll(om[r]);
+        c0 += __popcll(cm[r]);
+        if (s >= n) continue;
+        slot_oct[s] = o;
+        if ((om[r] >> lane) & 1) {
+            oct_start[o] = (int32_t)s;
+            oct_bits[o] = (uint8_t)(key[r] & 7);
+            poct[o] = o;
+            minidx[o] = perm[s];
+        }
+        if ((cm[r] >> lane) & 1) {
+            cell_oct[cl] = o;
+            cell_key[cl] = key[r] >> 3;
+        }
+        if (s == n - 1) {   // sentinels
+            oct_start[o + 1] = (int32_t)n;
+            cell_oct[cl + 1] = o + 1;
         }
     }
 }
@@ -158,11 +264,12 @@ RS_DEV int32_t lower_bound_u64(const uint64_t* __restrict__ keys, int32_t b, int
 }
 
 // row_start[r] = first cell whose row (key / nc) is >= r, for r in [0, rows]
-__global__ void k_row_start(const uint64_t* __restrict__ cell_key, int32_t n_cell, int64_t nc,
-                            int64_t rows, int32_t* __restrict__ row_start) {
+__global__ void k_row_start(const uint64_t* __restrict__ cell_key,
+                            const int32_t* __restrict__ counts, int64_t nc, int64_t rows,
+                            int32_t* __restrict__ row_start) {
     const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (r > rows) return;
-    row_start[r] = lower_bound_u64(cell_key, 0, n_cell, (uint64_t)r * (uint64_t)nc);
+    row_start[r] = lower_bound_u64(cell_key, 0, counts[1], (uint64_t)r * (uint64_t)nc);
 }
 
 struct LinkArgs {
@@ -171,22 +278,29 @@ struct LinkArgs {
     const int32_t* cell_oct;    // [n_cell + 1]
     const uint64_t* cell_key;   // [n_cell], ascending
     const int32_t* row_start;   // [nc^2 + 1], or null: rows found by binary search
-    int32_t n_cell;
+    const int32_t* counts;      // [0] octants, [1] cells
     const uint64_t* keys;       // sorted keys
     const float *sx, *sy, *sz;  // sorted positions
     int32_t* parent;            // union-find over octants (auto-link) or over slots
-    int32_t n_oct;
     Grid3 g;
     int2* heavy;                // deferred octant pairs (auto-link) ...
     int32_t* n_heavy;           // ... their count (may exceed the capacity)
     int32_t cap_heavy;
+    int64_t heavy_pairs;        // deferred above this many member pairs
 };
 
-// octant pairs with more member pairs than this are deferred to a second
-// pass, run one wavefront per pair once every lighter pair has been linked:
-// by then most of them already share a root, and the rest are searched 64
-// member pairs at a time instead of serially by one thread
-constexpr int64_t HEAVY_PAIRS = 1024;
+// Octant pairs with more than heavy_pairs member pairs are deferred to a
+// second pass, run one wavefront per pair once every lighter pair has been
+// linked: by then most of them already share a root, and the rest are
+// searched 64 member pairs at a time instead of serially by one thread.
+// While the octants do not fill the chip many times over, the pass ends with
+// its slowest thread, and a low limit shortens that (1M clustered particles
+// 1.63 -> 0.99 ms, 2.1M 1.85 -> 1.53 ms with 128 for 1024); beyond, the
+// slow threads are hidden and deferring costs more than it saves (30M
+// particles 13.05 ms with 1024, 13.2 with 256, 13.9 with 128).  With 32 the
+// queue overflows.
+constexpr int64_t HEAVY_FEW = 128, HEAVY_MANY = 1024;
+constexpr int32_t HEAVY_FEW_OCT = 1 << 22;   // octants up to which HEAVY_FEW holds
 
 // cells of row rr (cell indices [b, e))
 RS_DEV void row_cells(const LinkArgs& A, uint64_t rr, int32_t& b, int32_t& e) {
@@ -195,8 +309,8 @@ RS_DEV void row_cells(const LinkArgs& A, uint64_t rr, int32_t& b, int32_t& e) {
         e = A.row_start[rr + 1];
     } else {
         const uint64_t nc = (uint64_t)A.g.nc;
-        b = lower_bound_u64(A.cell_key, 0, A.n_cell, rr * nc);
-        e = lower_bound_u64(A.cell_key, b, A.n_cell, (rr + 1) * nc);
+        b = lower_bound_u64(A.cell_key, 0, A.counts[1], rr * nc);
+        e = lower_bound_u64(A.cell_key, b, A.counts[1], (rr + 1) * nc);
     }
 }
 
@@ -275,7 +389,7 @@ RS_DEV void link_cell(const LinkArgs& A, int32_t a, int32_t s0, int32_t s1, int 
                 __hip_atomic_store(A.parent + b, rb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (ra == rb) continue;
             const int32_t t0 = A.oct_start[b], t1 = A.oct_start[b + 1];
-            if ((int64_t)(s1 - s0) * (t1 - t0) > HEAVY_PAIRS) {
+            if ((int64_t)(s1 - s0) * (t1 - t0) > A.heavy_pairs) {
                 const int32_t q = atomicAdd(A.n_heavy, 1);
                 if (q < A.cap_heavy) {
                     A.heavy[q] = make_int2(a, b);
@@ -301,14 +415,24 @@ RS_DEV void link_cell(const LinkArgs& A, int32_t a, int32_t s0, int32_t s1, int 
     }
 }
 
-// one thread per octant: test it against every later octant in the
-// 27-cell neighbourhood.  Octants are numbered in cell-key order, so cells
+// One thread per octant: test it against every later octant in the 27-cell
+// neighbourhood; or (SPLIT) one thread per octant and neighbour cell, cell
+// blockIdx.y.  A thread's walk is a serial chain of dependent loads, 236 us
+// long even for a few thousand octants; a thread that walks all cells meets
+// most octants with its own root already known, which pays once the octants
+// fill the chip: split up to SPLIT_OCT octants (5000 particles 314 -> 179 us
+// a call, 250k clustered 1.36 -> 1.09 ms, 250k unclustered 222 -> 212 us), and
+// up to SPLIT_DENSE where octants hold 1.5 particles or more, so that the
+// walks are long (1M clustered 0.99 -> 0.77 ms, 2.1M 1.53 -> 1.42 ms; but 1M
+// unclustered 0.35 -> 0.43 ms).  Octants are numbered in cell-key order, so cells
 // with a smaller key (among them every cell of an earlier row) hold only
 // earlier octants, whose pairs with this one are taken from their side.
-template <bool AUTOLINK, bool PER, bool CNT>
+constexpr int32_t SPLIT_OCT = 1 << 18, SPLIT_DENSE = 1 << 21;
+
+template <bool AUTOLINK, bool PER, bool CNT, bool SPLIT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k_link(LinkArgs A) {
     const int32_t a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= A.n_oct) return;
+    if (a >= A.counts[0]) return;
     unsigned long long npairs = 0;   // counting build only
     const Grid3& g = A.g;
     const int32_t s0 = A.oct_start[a], s1 = A.oct_start[a + 1];
@@ -320,7 +444,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
     const int64_t cy = (int64_t)(row % (uint64_t)nc);
     const int64_t cz = (int64_t)(row / (uint64_t)nc);
 
-    if (!AUTOLINK) {
+    const int part = SPLIT ? (int)blockIdx.y : 0;
+    if (!AUTOLINK && (!SPLIT || part == 0)) {
         if (CNT) npairs += (unsigned long long)(s1 - s0) * (unsigned long long)(s1 - s0 - 1) / 2;
         for (int32_t i = s0; i < s1; i++) {
             const float xi = A.sx[i], yi = A.sy[i], zi = A.sz[i];
@@ -331,12 +456,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
     }
     int32_t ra = AUTOLINK ? a : s0;
     // x - 1 .. x + 1 are one contiguous key range unless x wraps
-    const bool inner = nc >= 3 && cx >= 1 && cx <= nc - 2;
-    for (int dz = -1; dz <= 1; dz++) {
+    const bool inner = !SPLIT && nc >= 3 && cx >= 1 && cx <= nc - 2;
+    const int dx0 = SPLIT ? part % 3 - 1 : -1, dx1 = SPLIT ? dx0 : 1;
+    const int dy0 = SPLIT ? part / 3 % 3 - 1 : -1, dy1 = SPLIT ? dy0 : 1;
+    const int dz0 = SPLIT ? part / 9 - 1 : -1, dz1 = SPLIT ? dz0 : 1;
+    for (int dz = dz0; dz <= dz1; dz++) {
         int64_t nz = cz + dz;
         if (!PER && (nz < 0 || nz >= nc)) continue;
         nz = nz < 0 ? nz + nc : (nz >= nc ? nz - nc : nz);
-        for (int dy = -1; dy <= 1; dy++) {
+        for (int dy = dy0; dy <= dy1; dy++) {
             int64_t ny = cy + dy;
             if (!PER && (ny < 0 || ny >= nc)) continue;
             ny = ny < 0 ? ny + nc : (ny >= nc ? ny - nc : ny);
@@ -356,7 +484,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                                                   dy, dz, ra, npairs);
                 }
             } else {
-                for (int dx = -1; dx <= 1; dx++) {
+                for (int dx = dx0; dx <= dx1; dx++) {
                     int64_t nx = cx + dx;
                     if (!PER && (nx < 0 || nx >= nc)) continue;
                     nx = nx < 0 ? nx + nc : (nx >= nc ? nx - nc : nx);
@@ -407,22 +535,56 @@ __global__ void __launch_bounds__(64) k_link_heavy(LinkArgs A) {
     if (CNT && lane == 0 && npairs) atomicAdd(&g_3d_pairs[blockIdx.x & 63], npairs);
 }
 
-// slot parents from the flattened octant roots: each slot points at the
-// first slot of its component's root octant (one slot per component is its
-// own parent, as with the slot-level union-find)
-__global__ void k_oct2slot(int64_t n, const int32_t* __restrict__ oflag,
-                           const int32_t* __restrict__ oex, const int32_t* __restrict__ oct_start,
-                           const int32_t* __restrict__ poct, int32_t* __restrict__ parent) {
-    int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const int32_t o = oex[s] + oflag[s] - 1;
-    parent[s] = oct_start[poct[o]];
-}
-
 __global__ void k_flatten(int64_t n, int32_t* __restrict__ parent) {
     int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (s >= n) return;
     parent[s] = uf_root(parent, (int)s);
+}
+
+// flattens the octants' union-find and lowers each root's smallest original
+// index to that of its octants (an octant that is no root keeps its own);
+// counts the roots.  Octants of one group are mostly adjacent, so the first
+// few roots of a wavefront are combined before their atomics; a root already
+// at or below an octant's index needs none.
+__global__ void __launch_bounds__(256)
+k_flatten_oct(const int32_t* __restrict__ counts, int32_t* __restrict__ poct,
+              int32_t* __restrict__ minidx, unsigned long long* __restrict__ nroots) {
+    __shared__ unsigned int part[4];
+    const int32_t o = blockIdx.x * 256 + threadIdx.x;
+    const bool in = o < counts[0];
+    const int32_t r = in ? uf_root(poct, o) : -1;
+    if (in) poct[o] = r;
+    const uint64_t roots = __ballot(in && r == o);
+    const int32_t key = in && r != o ? minidx[o] : 0x7fffffff;
+    bool todo = in && r != o && uf_load(minidx, r) > key;
+    uint64_t left = __ballot(todo);
+    for (int k = 0; k < 4 && left; k++) {
+        const int leader = __ffsll((unsigned long long)left) - 1;
+        const int32_t lr = __shfl(r, leader, 64);
+        const bool mine = todo && r == lr;
+        const uint32_t mn = wave_min_u32(mine ? (uint32_t)key : 0xffffffffu);
+        if ((int)(threadIdx.x & 63) == leader) atomicMin(minidx + lr, (int32_t)mn);
+        todo = todo && !mine;
+        left = __ballot(todo);
+    }
+    if (todo) atomicMin(minidx + r, key);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = (unsigned int)__popcll(roots);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned int b = part[0] + part[1] + part[2] + part[3];
+        if (b) atomicAdd(nroots, (unsigned long long)b);
+    }
+}
+
+// labels in the caller's order from the octants' roots (nothing when a
+// coordinate was out of range)
+__global__ void k_oct_labels(int64_t n, const int32_t* __restrict__ err,
+                             const int32_t* __restrict__ slot_oct,
+                             const int32_t* __restrict__ poct, const int32_t* __restrict__ perm,
+                             const int32_t* __restrict__ minidx, int32_t* __restrict__ labels) {
+    const int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (s >= n || *err) return;
+    labels[perm[s]] = minidx[poct[slot_oct[s]]];
 }
 
 // smallest original index per root; sorted slots of one group are mostly
@@ -454,10 +616,11 @@ constexpr int WL_BLOCKS = 4096;
 
 __global__ void __launch_bounds__(256)
 k_write_labels(int64_t n, const int32_t* __restrict__ parent, const int32_t* __restrict__ perm,
-               const int32_t* __restrict__ minidx, int32_t* __restrict__ labels,
-               unsigned long long* __restrict__ nroots) {
+               const int32_t* __restrict__ minidx, const int32_t* __restrict__ err,
+               int32_t* __restrict__ labels, unsigned long long* __restrict__ nroots) {
     __shared__ unsigned long long part[4];
     unsigned long long mine = 0;
+    if (*err) return;
     for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < n;
          s += (int64_t)gridDim.x * blockDim.x) {
         const int32_t r = parent[s];
@@ -532,26 +695,30 @@ size_t fof3d_bytes(int64_t n, const Grid3& g) {
 }
 
 template <bool PER, bool CNT>
-static int link_launch(const LinkArgs& A, unsigned go, hipStream_t st) {
+static int link_launch(const LinkArgs& A, int64_t n, int32_t max_oct, hipStream_t st) {
+    const dim3 one(grid_for(max_oct, 256, 1ll << 31)), split(one.x, 27);
+    const bool sp = max_oct <= SPLIT_OCT ||
+                    (max_oct <= SPLIT_DENSE && 2 * n >= 3 * (int64_t)max_oct);
     if (A.g.autolink) {
-        RS_TRY(fill_i32(A.n_heavy, 0, 1, st));
-        k_link<true, PER, CNT><<<go, 256, 0, st>>>(A);
+        if (sp) k_link<true, PER, CNT, true><<<split, 256, 0, st>>>(A);
+        else k_link<true, PER, CNT, false><<<one, 256, 0, st>>>(A);
         k_link_heavy<PER, CNT><<<HEAVY_BLOCKS, 64, 0, st>>>(A);
     } else {
-        k_link<false, PER, CNT><<<go, 256, 0, st>>>(A);
+        if (sp) k_link<false, PER, CNT, true><<<split, 256, 0, st>>>(A);
+        else k_link<false, PER, CNT, false><<<one, 256, 0, st>>>(A);
     }
     RS_HIP(hipGetLastError());
     return RS_OK;
 }
 
 template <bool PER>
-static int link_pass(const LinkArgs& A, unsigned go, hipStream_t st) {
-    if (!prof_count_pairs()) return link_launch<PER, false>(A, go, st);
+static int link_pass(const LinkArgs& A, int64_t n, int32_t max_oct, hipStream_t st) {
+    if (!prof_count_pairs()) return link_launch<PER, false>(A, n, max_oct, st);
     // counting build: counters cleared before, read back after (synchronous)
     unsigned long long h[64] = {0};
     RS_HIP(hipStreamSynchronize(st));
     RS_HIP(hipMemcpyToSymbol(HIP_SYMBOL(g_3d_pairs), h, sizeof(h)));
-    RS_TRY((link_launch<PER, true>(A, go, st)));
+    RS_TRY((link_launch<PER, true>(A, n, max_oct, st)));
     RS_HIP(hipMemcpyFromSymbolAsync(h, HIP_SYMBOL(g_3d_pairs), sizeof(h), 0,
                                     hipMemcpyDeviceToHost, st));
     RS_HIP(hipStreamSynchronize(st));
@@ -560,6 +727,12 @@ static int link_pass(const LinkArgs& A, unsigned go, hipStream_t st) {
     prof_add_count("pairs_fof3d", sum);
     return RS_OK;
 }
+
+// Up to this many particles the launches after the tables cover as many
+// octants as particles and read the counts on the device, which saves the
+// host's wait for them (some 25 us of a 400 us call); above, the idle threads
+// would cost more.
+constexpr int64_t FEW_PARTICLES = 1 << 16;
 
 // One 3D pass over the work space `ar` (at least fof3d_bytes(n, g), its bump
 // pointer at the start); `hcnt` is host memory for 16 counters.  Range
@@ -571,6 +744,7 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
     const uint64_t rows = (uint64_t)g.nc * (uint64_t)g.nc;
     const bool row_table = use_row_table(n, g);
     const int64_t cap_heavy = n / 4 + 1024;
+    const int64_t ntiles = (n + OT_TILE - 1) / OT_TILE;
     // the sort's keys and indices in share one region, which holds the
     // interleaved positions once the sort has consumed them
     char* kreg = take<char>(ar, 12 * (size_t)n);
@@ -582,10 +756,8 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
     float* sx = take<float>(ar, n);
     float* sy = take<float>(ar, n);
     float* sz = take<float>(ar, n);
-    int32_t* oflag = take<int32_t>(ar, n);
-    int32_t* cflag = take<int32_t>(ar, n);
-    int32_t* oex = take<int32_t>(ar, n);
-    int32_t* cex = take<int32_t>(ar, n);
+    int32_t* slot_oct = take<int32_t>(ar, n);
+    unsigned long long* sums = take<unsigned long long>(ar, ntiles);
     int32_t* oct_start = take<int32_t>(ar, n + 1);
     uint8_t* oct_bits = take<uint8_t>(ar, n + 1);
     int32_t* cell_oct = take<int32_t>(ar, n + 1);
@@ -594,11 +766,10 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
     int32_t* minidx = take<int32_t>(ar, n);
     int32_t* poct = take<int32_t>(ar, n + 1);
     int2* heavy = take<int2>(ar, cap_heavy);
-    int32_t* n_heavy = take<int32_t>(ar, 16);
     int32_t* row_start = row_table ? take<int32_t>(ar, rows + 1) : nullptr;
     size_t stb = sort_temp_bytes(n);
     void* stemp = arena_take(ar, stb);
-    void* ctemp = arena_take(ar, scan_temp_bytes(n));
+    // counters: 0 err, 1 octants, 2 cells, 3 deferred octant pairs, 4..5 groups
     int32_t* cnt = take<int32_t>(ar, 16);
     if (!cnt) return RS_EINTERNAL;
 
@@ -609,31 +780,25 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
     RS_TRY(sort_pairs_u64_i32(kin, kout, vin, perm, n, g.key_bits, stemp, stb, st));
     k_interleave3<<<gb, BT, 0, st>>>(n, x, y, z, prec);
     k_gather3<<<gb, BT, 0, st>>>(perm, prec, n, sx, sy, sz);
-    k_run_flags<<<gb, BT, 0, st>>>(kout, n, oflag, cflag);
-    RS_HIP(hipGetLastError());
-    RS_TRY(scan_exclusive_i32(oflag, oex, n, ctemp, cnt + 1, st));
-    RS_TRY(scan_exclusive_i32(cflag, cex, n, ctemp, cnt + 2, st));
-    RS_HIP(hipMemcpyAsync(hcnt, cnt, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    RS_HIP(hipStreamSynchronize(st));
-    if (hcnt[0]) return RS_ERANGE;
-    int32_t n_oct = hcnt[1], n_cell = hcnt[2];
-
-    k_tables<<<gb, BT, 0, st>>>(kout, n, oflag, oex, cflag, cex, oct_start, oct_bits, cell_oct,
-                                cell_key);
-    RS_HIP(hipGetLastError());
-    // sentinels: oct_start[n_oct] = n, cell_oct[n_cell] = n_oct
-    RS_TRY(fill_i32(oct_start + n_oct, (int32_t)n, 1, st));
-    RS_TRY(fill_i32(cell_oct + n_cell, n_oct, 1, st));
+    k_oct_sums<<<(unsigned)ntiles, OT_T, 0, st>>>(kout, n, sums);
+    k_oct_scan<<<1, OS_T, 0, st>>>(ntiles, sums, cnt + 1);
+    k_oct_tables<<<(unsigned)ntiles, OT_T, 0, st>>>(kout, n, sums, perm, oct_start, oct_bits,
+                                                    cell_oct, cell_key, slot_oct, poct, minidx);
     if (row_table)
         k_row_start<<<grid_for((int64_t)rows + 1, BT, 1ll << 31), BT, 0, st>>>(
-            cell_key, n_cell, g.nc, (int64_t)rows, row_start);
-    unsigned go = grid_for(n_oct, 256, 1ll << 31);
-    if (g.autolink) {
-        k_iota<<<go, 256, 0, st>>>(n_oct, poct);
-    } else {
-        k_iota<<<gb, BT, 0, st>>>(n, parent);
-    }
+            cell_key, cnt + 1, g.nc, (int64_t)rows, row_start);
     RS_HIP(hipGetLastError());
+    int32_t max_oct = (int32_t)n;
+    if (n > FEW_PARTICLES) {
+        RS_HIP(hipMemcpyAsync(hcnt, cnt, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        RS_HIP(hipStreamSynchronize(st));
+        if (hcnt[0]) return RS_ERANGE;
+        max_oct = hcnt[1];
+    }
+    if (!g.autolink) {
+        k_iota<<<gb, BT, 0, st>>>(n, parent);
+        RS_HIP(hipGetLastError());
+    }
 
     int64_t qcap = std::min<int64_t>(cap_heavy, INT32_MAX);
     // test hook: a smaller queue sends the pairs beyond it down the inline path
@@ -641,28 +806,31 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
         const int64_t v = atoll(e);
         if (v >= 0 && v < qcap) qcap = v;
     }
-    LinkArgs A{oct_start, oct_bits, cell_oct, cell_key, row_start, n_cell, kout, sx, sy, sz,
-               g.autolink ? poct : parent, n_oct, g, heavy, n_heavy, (int32_t)qcap};
+    LinkArgs A{oct_start, oct_bits, cell_oct, cell_key, row_start, cnt + 1, kout, sx, sy, sz,
+               g.autolink ? poct : parent, g, heavy, cnt + 3, (int32_t)qcap,
+               max_oct <= HEAVY_FEW_OCT ? HEAVY_FEW : HEAVY_MANY};
     if (instrument) prof_begin("fof3d_link", st);
-    RS_TRY(B.periodic ? link_pass<true>(A, go, st) : link_pass<false>(A, go, st));
+    RS_TRY(B.periodic ? link_pass<true>(A, n, max_oct, st)
+                       : link_pass<false>(A, n, max_oct, st));
     if (instrument) prof_end("fof3d_link", st, (double)n);
 
+    unsigned long long* nroots = reinterpret_cast<unsigned long long*>(cnt + 4);
     if (g.autolink) {
-        k_flatten<<<go, 256, 0, st>>>(n_oct, poct);
-        k_oct2slot<<<gb, BT, 0, st>>>(n, oflag, oex, oct_start, poct, parent);
+        k_flatten_oct<<<grid_for(max_oct, 256, 1ll << 31), 256, 0, st>>>(cnt + 1, poct, minidx,
+                                                                         nroots);
+        k_oct_labels<<<gb, BT, 0, st>>>(n, cnt, slot_oct, poct, perm, minidx, labels);
     } else {
         k_flatten<<<gb, BT, 0, st>>>(n, parent);
+        RS_TRY(fill_i32(minidx, 0x7fffffff, n, st));
+        k_min_index<<<gb, BT, 0, st>>>(n, parent, perm, minidx);
+        k_write_labels<<<grid_for(n, 256, WL_BLOCKS), 256, 0, st>>>(n, parent, perm, minidx, cnt,
+                                                                   labels, nroots);
     }
-    RS_TRY(fill_i32(minidx, 0x7fffffff, n, st));
-    k_min_index<<<gb, BT, 0, st>>>(n, parent, perm, minidx);
-    unsigned long long* nroots = reinterpret_cast<unsigned long long*>(cnt + 4);
-    k_write_labels<<<grid_for(n, 256, WL_BLOCKS), 256, 0, st>>>(n, parent, perm, minidx, labels,
-                                                               nroots);
     RS_HIP(hipGetLastError());
-    unsigned long long* hroots = reinterpret_cast<unsigned long long*>(hcnt + 4);
-    RS_HIP(hipMemcpyAsync(hroots, nroots, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+    RS_HIP(hipMemcpyAsync(hcnt, cnt, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     RS_HIP(hipStreamSynchronize(st));
-    if (n_groups) *n_groups = (int64_t)*hroots;
+    if (hcnt[0]) return RS_ERANGE;
+    if (n_groups) *n_groups = (int64_t)*reinterpret_cast<unsigned long long*>(hcnt + 4);
     return RS_OK;
 }
 
