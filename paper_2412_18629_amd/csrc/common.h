@@ -175,6 +175,10 @@ RS_DEV uint32_t wave_min_u32(uint32_t v) {
 
 constexpr float LB_EPS = 3.814697265625e-06f;
 constexpr float NORM_PAD = 1e30f;   // value of absent rows and columns
+// Across a periodic face X also carries the absolute rounding of the image
+// shift, at most eta = sqrt(a) box_slack(L) per pair of positions, and
+// (D + eta)^2 <= (1 + k) D^2 + (1 + 1/k) eta^2.
+constexpr float LB_WRAP = 0.0078125f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 

@@ -106,6 +106,16 @@ struct TreeBuf {
     int32_t cap_inode, cap_entry;
 };
 
+// Normalised coordinates of a level's members in tile order, for the lower
+// bounds by matrix products (common.h): X = sqrt(a) (x - centre), sqrt(c)
+// (v - mean) of the member's node.  a: x y z u per member, b: v w and the
+// scaled squared norm.  They take the place of the level's sort keys and of
+// the sort's scratch arrays, which are dead once the tree is built; reads past
+// a leaf's end (at most 63 members) stay inside the work space.
+struct XRows {
+    float *a, *b;
+};
+
 struct TArgs {
     const int32_t* mnode;    // [members] node of each member (tile order)
     const int32_t* tile_node;
@@ -116,6 +126,7 @@ struct TArgs {
     Members T;
     PhaseParams pp;
     int64_t nmem;            // members at this level
+    XRows X;                 // their normalised coordinates
 };
 
 // Absolute slack of the box lower bounds on unwrapped positions: it covers
@@ -144,18 +155,19 @@ bool use_o32(int64_t nmem);
 
 int tree_build(TreeBuf& tb, int32_t* root, const uint64_t* skeys, const LNode* nodes, int nv,
                const Members& T, const int32_t* mnode, const LParam* prm,
-               const PhaseParams& pp, std::vector<int32_t>* level_begin, bool* overflow,
+               const PhaseParams& pp, const XRows& X, std::vector<int32_t>* level_begin, bool* overflow,
                int32_t* n_entry_out, hipStream_t st);
 // refits the leaf and internal boxes to the members with d_i^2 <= l^2 (after
 // the select, before linking)
 int tree_refit_active(TreeBuf& tb, int32_t n_entry, const std::vector<int32_t>& level_begin,
                       const Members& T, const int32_t* mnode, const LParam* prm,
                       const PhaseParams& pp, const float* d2, hipStream_t st);
-// chunk length: whole rounds stay at least 64 so the XCDs finish together;
-// the longest chunk comes from the tuning table
+// chunk length: whole rounds stay at least 16 so the XCDs finish together
+// (rounds of 16, 64, 256 and 1024: the NN of a 256^3 hierarchy takes 36.4,
+// 38.0, 40.3 and 44.3 ms); the longest chunk comes from the tuning table
 inline int xcd_chunk(int ntiles) {
     const int cap = tune_get(TUNE_XCD_CHUNK);
-    int c = ntiles / (64 * XCDS);
+    int c = ntiles / (16 * XCDS);
     return c < 1 ? 1 : (c > cap ? cap : c);
 }
 

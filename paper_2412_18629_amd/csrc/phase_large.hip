@@ -909,16 +909,19 @@ int large_level(LargeWork* w, const std::vector<ChildOut>& hn, const Members& in
     // search tree; its buffers grow and the build is redone on overflow
     if (w->tb.cap_entry == 0) RS_TRY(tree_reserve(w, w->cap_m, w->cap_nodes, 1));
     int32_t n_entry = 0;
+    // the tree's last kernel writes them, when the keys (kin, kout: one run
+    // of 16 bytes a member) and the sort's scratch have been read
+    const XRows xr{reinterpret_cast<float*>(w->kin), static_cast<float*>(w->sort_temp)};
     for (int64_t grow = 2;; grow *= 2) {
         bool tree_overflow = false;
-        RS_TRY(tree_build(w->tb, w->root, w->kout, w->nodes, nv, w->T, w->mnode, w->prm, pp,
+        RS_TRY(tree_build(w->tb, w->root, w->kout, w->nodes, nv, w->T, w->mnode, w->prm, pp, xr,
                           &tree_levels, &tree_overflow, &n_entry, st));
         if (!tree_overflow) break;
         if (grow > 1024) return RS_EINTERNAL;
         RS_TRY(tree_reserve(w, w->cap_m, w->cap_nodes, grow));
     }
     TArgs TA{w->mnode, w->tile_node, w->nodes, w->prm, w->root, w->tb, w->T, pp,
-             M};
+             M, xr};
     // proposer features (when requested or when a proposal is wanted)
     const bool learned = w->model != nullptr;
     if (pp.want_feat || learned) {

@@ -53,11 +53,6 @@ constexpr int QCAP = 128;         // queued pairs per wavefront
 constexpr int N_ROWS = 7;         // X of x y z u v w, squared norm
 constexpr float NORM_WIDE = 1e29f;
 
-// Across a periodic face X also carries the absolute rounding of the image
-// shift, at most eta = sqrt(a) box_slack(L) per pair of positions, and
-// (D + eta)^2 <= (1 + k) D^2 + (1 + 1/k) eta^2.
-constexpr float LB_WRAP = 0.0078125f;
-
 constexpr int n_stride(int maxn) { return maxn + 16; }   // rows on different banks
 
 // Per member 36 bytes: the seven rows (whose space holds the component

@@ -1,27 +1,31 @@
-// phase_tile.hip -- tile-cooperative searches over the 6D tree.
+// phase_tile.hip -- tile-cooperative linking over the 6D tree.
 //
 // One wavefront owns a tile of 64 consecutive members (one query per lane).
 // It walks the tree ONCE with the bounding box of its queries, collecting
-// every leaf that any query could need into an LDS list.  Each listed leaf
-// is then loaded once (one member per lane) and only the queries whose own
-// exact bound admits the leaf are replayed against it: each such query is
-// broadcast to the lanes, every lane evaluates the pair with its member.
-// Candidate data is read once per tile instead of once per query.  The walk
-// scans up to four stack entries per pass (cells average about ten
-// children), and linked pairs are united in batches of 64.
-#include <type_traits>
-
+// every leaf that any query could need into an LDS list (up to four stack
+// entries per pass: cells average about ten children).  Up to 64 listed
+// leaves at a time, one per lane, are then bounded against every query; each
+// admitted leaf is read once and screened by matrix products against the
+// queries that admit it (see k_tile_link), and the pairs that the screening
+// cannot exclude are evaluated exactly and united, 64 at a time.
+//
+// What bounds it: latency (vector unit 40 % busy, matrix cores 20 %), half of
+// it the union-find's dependent reads.  512^3 workload, all levels: 199 -> 138 ms.
+// Deeply nested 9.1M particles 34.2 -> 16 ms (23 ms with the products alone;
+// the rest from ending a pair at equal parents, see unite_pair), 256^3 15.0
+// -> 9.1 ms.  Loading the next leaf's operands ahead measured the same.
 #include "phase_common.h"
 
 namespace rs {
 
-// LDS per wavefront stays under 5 KB, so that eight wavefronts fit per SIMD:
-// the link is bound by the latency of its walks and replays, and more
-// resident wavefronts hide more of it than larger buffers save
+// LDS per wavefront stays small enough for seven wavefronts per SIMD (the
+// registers allow six): more of them hide more latency than larger buffers
+// save
 constexpr int TSTACK = 520;   // >= 64 internal children x 8 levels
-constexpr int TLIST = 96;     // candidate leaves buffered before processing (>= 64)
+constexpr int TLIST = 128;    // candidate leaves buffered (up to 63, and one pass)
 constexpr int THITS = 64;     // linked pairs buffered before their unions (>= 64)
-static_assert(TLIST >= 64 && THITS >= 64, "one pass adds up to 64 leaves or pairs");
+static_assert(TLIST >= 127 && THITS == 64, "one pass adds up to 64 leaves or pairs");
+constexpr int QS = 68;        // row stride of the queries' coordinates
 
 struct TileRec {
     float lo[6], hi[6];
@@ -77,9 +81,78 @@ struct TStackEnt {
     int32_t cfirst, ccount;
 };
 
-// value of lane src (uniform) in every lane, through the scalar unit
-RS_DEV float bcast(float v, int src) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
+// A pushed cell in LDS.  In the compact form (below 2^26 child records) four
+// bytes: the first child's record below the count of 1 to 63 children, or 0
+// and the cell's own record, from which the range is read back.
+template <bool COMPACT>
+struct TSlot;
+template <>
+struct TSlot<true> {
+    uint32_t v;
+    static RS_DEV TSlot pack(int32_t rec, int32_t cfirst, int32_t ccount) {
+        return ccount < 64 ? TSlot{(uint32_t)ccount << 26 | (uint32_t)cfirst} : TSlot{(uint32_t)rec};
+    }
+    RS_DEV TStackEnt unpack(const float* __restrict__ erec) const {
+        const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+        TStackEnt e{(int32_t)(u & 0x3ffffffu), (int32_t)(u >> 26)};
+        if (e.ccount == 0) {
+            const int2 c = *reinterpret_cast<const int2*>(erec + 16 * (int64_t)e.cfirst + 14);
+            e = TStackEnt{__builtin_amdgcn_readfirstlane(c.x), __builtin_amdgcn_readfirstlane(c.y)};
+        }
+        return e;
+    }
+};
+template <>
+struct TSlot<false> {
+    int32_t cfirst, ccount;
+    static RS_DEV TSlot pack(int32_t, int32_t cfirst, int32_t ccount) {
+        return TSlot{cfirst, ccount};
+    }
+    RS_DEV TStackEnt unpack(const float* __restrict__) const { return TStackEnt{cfirst, ccount}; }
+};
+
+// sum over the 64 lanes, in every lane (counting build)
+RS_DEV int32_t wave_sum_i32(int32_t v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// an element of the normalised rows (below 2^28 members a 32-bit byte offset)
+template <bool O32>
+RS_DEV float xload(const float* __restrict__ base, int64_t i, int off = 0) {
+    if constexpr (O32)
+        return (reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) +
+                                               ((uint32_t)i << 2)))[off];
+    else
+        return base[i + off];
+}
+
+// Unites the components of a and b, whose parents pa and pb have just been
+// read.  Both walks advance together, and both ends are left pointing at the
+// root they found (a non-root's parent is only ever replaced by an ancestor),
+// so that most of the many pairs inside one component end at the comparison
+// of their parents.
+RS_DEV void unite_pair(int* par, int a, int b, int pa, int pb) {
+    int ra = pa, rb = pb;
+    for (;;) {
+        const int na = uf_load(par, ra), nb = uf_load(par, rb);
+        if (na != ra || nb != rb) {
+            ra = na;
+            rb = nb;
+            if (ra != rb) continue;
+        }
+        if (ra == rb) break;
+        const int lo = min(ra, rb), hi = max(ra, rb);
+        const int old = atomicCAS(par + hi, hi, lo);
+        ra = lo;
+        rb = old == hi ? lo : old;
+        if (ra == rb) break;
+    }
+    if (pa != ra && a != ra)
+        __hip_atomic_store(par + a, ra, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (pb != ra && b != ra)
+        __hip_atomic_store(par + b, ra, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Links within l among later members.  One wavefront per tile of 64
@@ -91,12 +164,15 @@ RS_DEV float bcast(float v, int src) {
 __device__ unsigned long long g_link_pairs[64];
 
 template <bool O32, bool CNT>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64, 6)
 k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
             int32_t* __restrict__ par) {
-    __shared__ TStackEnt stk[TSTACK];
+    __shared__ TSlot<O32> stk[TSTACK];
     __shared__ int32_t list[TLIST];
     __shared__ int2 hits[THITS];
+    __shared__ float qX[8 * QS];     // -2 X of the queries, 1, scaled norm less the threshold
+    __shared__ float tbox[12];       // box of the active queries
+    __shared__ int32_t col[16];      // query of each column
     const int lane = threadIdx.x;
     const int t = xcd_chunk_index(blockIdx.x, chunk);
     if (t >= ntiles) return;
@@ -115,20 +191,51 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
     const int64_t mq = ts + lane;
     const bool valid = mq < te;
     const int64_t mm = valid ? mq : ts;
-    const float qx = mload<O32>(T.x, mm), qy = mload<O32>(T.y, mm), qz = mload<O32>(T.z, mm);
-    const float qu = mload<O32>(T.vx, mm), qv = mload<O32>(T.vy, mm), qw = mload<O32>(T.vz, mm);
     const bool act = valid && mload<O32>(d2, mm) <= l2;
     const uint64_t amask = __ballot(act);
     if (!amask) return;
-    const float w[3] = {min_image(qx - P.rx, pp.L, pp.h), min_image(qy - P.ry, pp.L, pp.h),
-                        min_image(qz - P.rz, pp.L, pp.h)};
-    const float qpt[6] = {w[0], w[1], w[2], qu, qv, qw};
-    // box of the active queries
-    float blo[6], bhi[6];
+    // its place in the boxes' frame, loaded where it is needed (registers
+    // decide how many wavefronts hide each other's latencies here)
+    auto load_query = [&](float q[6]) {
+        q[0] = min_image(mload<O32>(T.x, mm) - P.rx, pp.L, pp.h);
+        q[1] = min_image(mload<O32>(T.y, mm) - P.ry, pp.L, pp.h);
+        q[2] = min_image(mload<O32>(T.z, mm) - P.rz, pp.L, pp.h);
+        q[3] = mload<O32>(T.vx, mm);
+        q[4] = mload<O32>(T.vy, mm);
+        q[5] = mload<O32>(T.vz, mm);
+    };
+    {
+        float q[6];
+        load_query(q);
 #pragma unroll
-    for (int d = 0; d < 6; d++) {
-        blo[d] = tw_min(act ? qpt[d] : __builtin_huge_valf());
-        bhi[d] = tw_max(act ? qpt[d] : -__builtin_huge_valf());
+        for (int d = 0; d < 6; d++) {
+            const float lo = tw_min(act ? q[d] : __builtin_huge_valf());
+            const float hi = tw_max(act ? q[d] : -__builtin_huge_valf());
+            if (lane == 0) {
+                tbox[d] = lo;
+                tbox[6 + d] = hi;
+            }
+        }
+    }
+    // a pair is a candidate when its bound does not exceed l^2 (with the slack
+    // of image shifts where the node has them); the tiny constant makes the
+    // difference negative for coinciding points at l = 0
+    const int lm = lane & 15, lk = lane >> 4, lkb = lk < 2 ? lk : 2;
+    float reach, l2x4;
+    {
+        const float eta = sqrtf(P.a) * box_slack(pp.L);
+        const float thr = P.nowrap ? l2 : l2 * (1.0f + LB_WRAP) +
+                                              (1.0f + 1.0f / LB_WRAP) * 1.001f * eta * eta;
+        reach = sqrtf(thr);
+        l2x4 = 4.0f * (thr * 1.00001f + 1e-30f);
+#pragma unroll
+        for (int k = 0; k < 4; k++) qX[k * QS + lane] = -2.0f * xload<O32>(A.X.a, 4 * mm + k);
+#pragma unroll
+        for (int k = 0; k < 2; k++) qX[(4 + k) * QS + lane] = -2.0f * xload<O32>(A.X.b, 3 * mm + k);
+        qX[6 * QS + lane] = 1.0f;
+        qX[7 * QS + lane] = xload<O32>(A.X.b, 3 * mm + 2) - (thr * 1.000001f + 1e-30f);
+        if (lane < 8) qX[lane * QS + 64] = lane < 6 ? 0.0f : lane == 6 ? 1.0f : NORM_PAD;
+        if (lane < 16) col[lane] = 0;
     }
     const int64_t first_act = ts + __ffsll((unsigned long long)amask) - 1;
 
@@ -136,22 +243,33 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
     unsigned long long npairs = 0;   // counting build only
     auto unite_hits = [&]() {
         __syncthreads();
-        for (int i = lane; i < nhit; i += 64) uf_unite(par, hits[i].x, hits[i].y);
+        if (lane < nhit) {
+            const int2 p = hits[lane];
+            const int pa = uf_load(par, p.x), pb = uf_load(par, p.y);
+            if (pa != pb) {   // else one component already
+                const float d = phase_d2<true>(
+                    mload<O32>(T.x, p.x), mload<O32>(T.y, p.x), mload<O32>(T.z, p.x),
+                    mload<O32>(T.vx, p.x), mload<O32>(T.vy, p.x), mload<O32>(T.vz, p.x),
+                    mload<O32>(T.x, p.y), mload<O32>(T.y, p.y), mload<O32>(T.z, p.y),
+                    mload<O32>(T.vx, p.y), mload<O32>(T.vy, p.y), mload<O32>(T.vz, p.y), P.a,
+                    P.c, pp.L, pp.h);
+                if (d <= l2) unite_pair(par, p.x, p.y, pa, pb);
+            }
+        }
         nhit = 0;
         __syncthreads();
     };
 
-    // one pass over the buffered candidate leaves: per leaf, the queries
-    // whose own bound admits it are replayed against its members.  The pair
-    // test runs on every lane (a lane past the leaf's end holds a valid
-    // member and is masked afterwards), so the replay has no divergent branch.
-    auto process = [&](int n, auto nowrap) {
-        constexpr bool NOWRAP = decltype(nowrap)::value;
+    // Nodes that percolate (no culling): per buffered leaf, every active query is
+    // replayed against the members, on all lanes (a lane past the leaf's end
+    // holds a valid member and is masked afterwards).
+    auto replay = [&](int n) {
+        const float qx = mload<O32>(T.x, mm), qy = mload<O32>(T.y, mm), qz = mload<O32>(T.z, mm);
+        const float qu = mload<O32>(T.vx, mm), qv = mload<O32>(T.vy, mm),
+                    qw = mload<O32>(T.vz, mm);
         for (int li = 0; li < n; li++) {
             const TileRec r = trec_load(tb.erec, list[li]);
-            bool need = act && r.end > mq + 1;
-            if (need && cull) need = !(box_box_lb(qpt, qpt, r, P.a, P.c) > l2);
-            uint64_t mk = __ballot(need);
+            uint64_t mk = __ballot(act && r.end > mq + 1);
             if (!mk) continue;
             const int64_t mj = r.start + lane;
             const bool has = mj < r.end;
@@ -167,10 +285,9 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
             while (mk) {
                 const int src = __ffsll((unsigned long long)mk) - 1;
                 mk &= mk - 1;
-                const float bx = bcast(qx, src), by = bcast(qy, src), bz = bcast(qz, src);
-                const float bu = bcast(qu, src), bv = bcast(qv, src), bw = bcast(qw, src);
-                const float dd = phase_d2<!NOWRAP>(bx, by, bz, bu, bv, bw, xj, yj, zj, uj, vj,
-                                                   wj, P.a, P.c, pp.L, pp.h);
+                const float dd = phase_d2<true>(lane_f(qx, src), lane_f(qy, src), lane_f(qz, src),
+                                                lane_f(qu, src), lane_f(qv, src), lane_f(qw, src),
+                                                xj, yj, zj, uj, vj, wj, P.a, P.c, pp.L, pp.h);
                 const int32_t k0 = off + src;
                 const uint64_t later = k0 <= 0 ? hasm : (k0 >= 64 ? 0ull : hasm & (~0ull << k0));
                 if (CNT) npairs += (unsigned long long)__popcll(later);
@@ -186,31 +303,182 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
         }
     };
 
+    // Up to 64 buffered leaves at a time, one per lane: every active query is
+    // broadcast and bounded against all of them, which leaves each lane the
+    // mask of the queries that admit its leaf.  Per admitted leaf the queries
+    // are gathered into the columns of 16-wide tiles, and lower bounds of d^2
+    // less the threshold of all their pairs with the leaf's members come from
+    // two matrix products per 16 members.  The sign bits of a lane's sixteen
+    // results are its candidates; they are queued and evaluated exactly before
+    // they are united.
+    auto screen = [&](int n) {
+        const bool in = lane < n;
+        const TileRec r = trec_load(tb.erec, list[in ? lane : 0]);
+        const int32_t rstart = r.start, rend = r.end;
+        // the leaf's box in the frame of qX (-2 X), widened by what rounding
+        // X can take from a difference (2 units of 2^-24 of either end's X,
+        // and the shift from the reference member to the centre, at most two
+        // of the eight units of L that the stored box is wider by)
+        float lo[6], hi[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            const float s = k < 3 ? P.sa : P.sc;
+            const float o = k == 0 ? P.rx - P.cx : k == 1 ? P.ry - P.cy : k == 2 ? P.rz - P.cz
+                            : k == 3 ? -P.cu : k == 4 ? -P.cv : -P.cw;
+            const float x0 = s * (r.lo[k] + o), x1 = s * (r.hi[k] + o);
+            const float e = 2e-6f * (fmaxf(fabsf(x0), fabsf(x1)) + reach);
+            lo[k] = -2.0f * (x1 + e);
+            hi[k] = -2.0f * (x0 - e);
+        }
+        // lane q: the leaves that query q admits.  A step bounds one query
+        // against all leaves (some 23 vector instructions, coordinates
+        // broadcast from LDS) or one leaf against all queries (some 33, box
+        // broadcast from its lane), whichever set is cheaper to go through.
+        uint64_t adm = 0;
+        uint32_t glo = 0, ghi = 0;
+        if (23 * __popcll(amask) < 33 * n) {
+            for (uint64_t left = amask; left; left &= left - 1) {
+                const int q = __builtin_ctzll(left);
+                float g2 = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 6; k++) {
+                    const float p = qX[k * QS + q];
+                    const float g = p - __builtin_amdgcn_fmed3f(p, lo[k], hi[k]);
+                    g2 = fmaf(g, g, g2);
+                }
+                const uint64_t m = __ballot(in && g2 <= l2x4);
+                adm |= m;
+                if (lane == q) {
+                    glo = (uint32_t)m;
+                    ghi = (uint32_t)(m >> 32);
+                }
+            }
+        } else {
+            float p[6];
+#pragma unroll
+            for (int k = 0; k < 6; k++) p[k] = qX[k * QS + lane];
+            for (int j = 0; j < n; j++) {
+                float g2 = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 6; k++) {
+                    const float g =
+                        p[k] - __builtin_amdgcn_fmed3f(p[k], lane_f(lo[k], j), lane_f(hi[k], j));
+                    g2 = fmaf(g, g, g2);
+                }
+                const bool need = act && g2 <= l2x4;
+                adm |= __ballot(need) ? 1ull << j : 0ull;
+                if (j < 32) glo |= need ? 1u << j : 0u;
+                else ghi |= need ? 1u << (j - 32) : 0u;
+            }
+        }
+        // row operands: member start + 16 rb + lm, coordinates lk and 4 + lk
+        while (adm) {
+            const int src = __builtin_ctzll(adm);
+            adm &= adm - 1;
+            const int32_t start = __builtin_amdgcn_readlane(rstart, src);
+            const int32_t len = __builtin_amdgcn_readlane(rend, src) - start;
+            const uint64_t mk = __ballot(((src < 32 ? glo : ghi) >> (src & 31)) & 1u);
+            // all four row blocks, whatever the leaf's length (rows past its end
+            // are masked below): no branches between the products
+            const int64_t m = (int64_t)start + lm;
+            float a0[4], a1[4];
+#pragma unroll
+            for (int rb = 0; rb < 4; rb++) {
+                a0[rb] = xload<O32>(A.X.a, 4 * m + lk, 64 * rb);
+                a1[rb] = xload<O32>(A.X.b, 3 * m + lkb, 48 * rb);
+            }
+            const bool own = start < (int32_t)te;   // members of this tile or before it
+            if (CNT) {
+                const int32_t later = (mk >> lane) & 1
+                    ? max(start + len - (int32_t)max((int64_t)start, mq + 1), 0) : 0;
+                npairs += (unsigned long long)wave_sum_i32(later);
+            }
+            // results 4 rb + t of a lane, the first in bit 15, are rows
+            // 16 rb + 4 lk + t
+            const uint32_t rows =
+                (0xffff0000u >> (4 * (len >> 4) + min(max((len & 15) - 4 * lk, 0), 4))) & 0xffffu;
+            const int nq = __popcll(mk);
+            const int rank0 = __popcll(mk & lanemask_lt());
+#pragma unroll
+            for (int rb = 0; rb < 4; rb++) a1[rb] = lk == 3 ? 1.0f : a1[rb];
+            for (int c0 = 0; c0 < nq; c0 += 16) {
+                const uint32_t rank = (uint32_t)(rank0 - c0);
+                if (((mk >> lane) & 1) && rank < 16u) col[rank] = lane;
+                __builtin_amdgcn_wave_barrier();
+                const int qc = col[lm];
+                const int q = c0 + lm < nq ? qc : 64;   // column 64: no query
+                __builtin_amdgcn_wave_barrier();
+                const float b0 = qX[lk * QS + q], b1 = qX[(4 + lk) * QS + q];
+                f32x4 o[4];
+                const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int rb = 0; rb < 4; rb++) o[rb] = mfma_16x16x4(a0[rb], b0, zero);
+#pragma unroll
+                for (int rb = 0; rb < 4; rb++) o[rb] = mfma_16x16x4(a1[rb], b1, o[rb]);
+                uint32_t bits = 0;
+#pragma unroll
+                for (int rb = 0; rb < 4; rb++)
+#pragma unroll
+                    for (int t = 0; t < 4; t++)
+                        bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(o[rb][t]), 31);
+                bits &= rows;
+                uint64_t any = __ballot(bits != 0);
+                while (any) {
+                    const int b = 16 - __ffs((int)bits);
+                    const int32_t i = (int32_t)ts + q;
+                    const int32_t j = start + 16 * (b >> 2) + 4 * lk + (b & 3);
+                    const bool ok = bits != 0 && (!own || j > i);
+                    const uint64_t hm = __ballot(ok);
+                    if (nhit + __popcll(hm) > THITS) unite_hits();
+                    if (ok) hits[nhit + __popcll(hm & lanemask_lt())] = make_int2(i, j);
+                    nhit += __popcll(hm);
+                    bits &= bits - 1;
+                    any = __ballot(bits != 0);
+                }
+            }
+        }
+    };
+    auto process = [&](int n) {
+        if (n == 0) return;   // nothing listed: no entry to read
+        __syncthreads();
+        if (cull) screen(n);
+        else replay(n);
+    };
+
     // walk the tree with the tile box; buffer leaves, flush when full
     int nlist = 0;
-    if (lane == 0) stk[0] = TStackEnt{tb.cfirst[A.root[v]], tb.ccount[A.root[v]]};
-    int sp = 1;
+    // a root is not a record: it is walked directly before anything is popped
+    TStackEnt se{tb.cfirst[A.root[v]], tb.ccount[A.root[v]]};
+    int sp = 0;
     __syncthreads();
-    while (sp > 0) {
+    for (;;) {
         // cells average about ten children: up to four entries whose
         // children fit in 64 lanes are scanned in one pass, each on its own
         // run of lanes (a pass pushes at most 64 entries, as one cell does)
-        sp--;
-        TStackEnt se = stk[sp];
         int32_t cf1 = 0, cf2 = 0, cf3 = 0, e1 = 64, e2 = 64, e3 = 64, tot = se.ccount;
-        if (tot <= 64) {
-            if (sp > 0 && tot + stk[sp - 1].ccount <= 64) {
-                cf1 = stk[--sp].cfirst;
+        if (sp > 0 && tot < 64) {
+            TStackEnt n1 = stk[sp - 1].unpack(tb.erec);
+            if (tot + n1.ccount <= 64) {
+                sp--;
+                cf1 = n1.cfirst;
                 e1 = tot;
-                tot += stk[sp].ccount;
-                if (sp > 0 && tot + stk[sp - 1].ccount <= 64) {
-                    cf2 = stk[--sp].cfirst;
-                    e2 = tot;
-                    tot += stk[sp].ccount;
-                    if (sp > 0 && tot + stk[sp - 1].ccount <= 64) {
-                        cf3 = stk[--sp].cfirst;
-                        e3 = tot;
-                        tot += stk[sp].ccount;
+                tot += n1.ccount;
+                if (sp > 0 && tot < 64) {
+                    n1 = stk[sp - 1].unpack(tb.erec);
+                    if (tot + n1.ccount <= 64) {
+                        sp--;
+                        cf2 = n1.cfirst;
+                        e2 = tot;
+                        tot += n1.ccount;
+                        if (sp > 0 && tot < 64) {
+                            n1 = stk[sp - 1].unpack(tb.erec);
+                            if (tot + n1.ccount <= 64) {
+                                sp--;
+                                cf3 = n1.cfirst;
+                                e3 = tot;
+                                tot += n1.ccount;
+                            }
+                        }
                     }
                 }
             }
@@ -230,27 +498,37 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
             if (b0 + lane < se.ccount) {
                 r = trec_load(tb.erec, k);
                 leaf = r.cfirst < 0;
+                float blo[6], bhi[6];
+#pragma unroll
+                for (int d = 0; d < 6; d++) {
+                    blo[d] = tbox[d];
+                    bhi[d] = tbox[6 + d];
+                }
                 need = r.end > first_act + 1 &&
                        (!cull || !(box_box_lb(blo, bhi, r, P.a, P.c) > l2));
             }
             const uint64_t imask = __ballot(need && !leaf);
             if (need && !leaf)
-                stk[sp + __popcll(imask & lanemask_lt())] = TStackEnt{r.cfirst, r.ccount};
+                stk[sp + __popcll(imask & lanemask_lt())] =
+                    TSlot<O32>::pack(k, r.cfirst, r.ccount);
             sp += __popcll(imask);
             const uint64_t lmask = __ballot(need && leaf);
-            if (nlist + __popcll(lmask) > TLIST) {
-                __syncthreads();
-                if (P.nowrap) process(nlist, std::true_type{});
-                else process(nlist, std::false_type{});
-                nlist = 0;
-            }
             if (need && leaf) list[nlist + __popcll(lmask & lanemask_lt())] = k;
             nlist += __popcll(lmask);
             __syncthreads();
+            if (nlist >= 64) {
+                process(64);
+                nlist -= 64;
+                const int32_t rest = lane < nlist ? list[64 + lane] : 0;
+                __syncthreads();
+                if (lane < nlist) list[lane] = rest;
+                __syncthreads();
+            }
         }
+        if (sp == 0) break;
+        se = stk[--sp].unpack(tb.erec);
     }
-    if (P.nowrap) process(nlist, std::true_type{});
-    else process(nlist, std::false_type{});
+    process(nlist);
     unite_hits();
     if (CNT && lane == 0 && npairs) atomicAdd(&g_link_pairs[blockIdx.x & 63], npairs);
 }
@@ -258,7 +536,9 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
 int tile_link(const TArgs& A, int ntiles, const float* d2, int32_t* par, hipStream_t st) {
     if (ntiles <= 0) return RS_OK;
     const int c = xcd_chunk(ntiles);
-    const bool o32 = use_o32(A.nmem);
+    // 32-bit offsets: four floats a member in the widest rows, and compact stack
+    // entries
+    const bool o32 = use_o32(4 * A.nmem) && A.tb.cap_entry < (1 << 26);
     const unsigned grid = xcd_chunk_grid(ntiles, c);
     if (!prof_count_pairs()) {
         if (o32) k_tile_link<true, false><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);

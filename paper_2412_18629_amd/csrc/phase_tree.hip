@@ -170,11 +170,11 @@ RS_DEV float wmin_nonneg(float x) {
     return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)v, 63));
 }
 
-// leaf boxes (wave per entry) and the leaf of every member; position
-// extents widened by the bounds' slack
+// leaf boxes (wave per entry), the leaf of every member and its normalised
+// coordinates; position extents widened by the bounds' slack
 __global__ void __launch_bounds__(256)
 k_tree_leafbox(int32_t n_entry, TreeBuf tb, Members T, const int32_t* __restrict__ mnode,
-               const LParam* __restrict__ prm, PhaseParams pp) {
+               const LParam* __restrict__ prm, PhaseParams pp, XRows xr) {
     const int lane = threadIdx.x & 63;
     const int32_t e = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (e >= n_entry || tb.enode[e] >= 0) return;
@@ -191,6 +191,18 @@ k_tree_leafbox(int32_t n_entry, TreeBuf tb, Members T, const int32_t* __restrict
         c[4] = T.vy[m];
         c[5] = T.vz[m];
         tb.leaf_of[m] = e;
+        const float sa = sqrtf(P.a), sc = sqrtf(P.c);
+        const float X[6] = {sa * min_image(T.x[m] - P.cx, pp.L, pp.h),
+                            sa * min_image(T.y[m] - P.cy, pp.L, pp.h),
+                            sa * min_image(T.z[m] - P.cz, pp.L, pp.h),
+                            sc * (c[3] - P.cu), sc * (c[4] - P.cv), sc * (c[5] - P.cw)};
+        float norm = X[0] * X[0];
+#pragma unroll
+        for (int k = 1; k < 6; k++) norm = fmaf(X[k], X[k], norm);
+        reinterpret_cast<float4*>(xr.a)[m] = make_float4(X[0], X[1], X[2], X[3]);
+        xr.b[3 * (int64_t)m] = X[4];
+        xr.b[3 * (int64_t)m + 1] = X[5];
+        xr.b[3 * (int64_t)m + 2] = norm * (1.0f - LB_EPS);
     }
     const float slack = box_slack(pp.L);
 #pragma unroll
@@ -610,8 +622,8 @@ __global__ void k_tree_roots(int nv, const LNode* __restrict__ nodes, TreeBuf tb
 
 int tree_build(TreeBuf& tb, int32_t* root, const uint64_t* skeys, const LNode* nodes, int nv,
                const Members& T, const int32_t* mnode, const LParam* prm,
-               const PhaseParams& pp, std::vector<int32_t>* level_begin, bool* overflow,
-               int32_t* n_entry_out, hipStream_t st) {
+               const PhaseParams& pp, const XRows& X, std::vector<int32_t>* level_begin,
+               bool* overflow, int32_t* n_entry_out, hipStream_t st) {
     *overflow = false;
     *n_entry_out = 0;
     int32_t* hc = nullptr;
@@ -646,7 +658,7 @@ int tree_build(TreeBuf& tb, int32_t* root, const uint64_t* skeys, const LNode* n
     RS_HIP(hipStreamSynchronize(st));
     const int32_t n_entry = hc[0];
     if (n_entry > 0) {
-        k_tree_leafbox<<<(n_entry + 3) / 4, 256, 0, st>>>(n_entry, tb, T, mnode, prm, pp);
+        k_tree_leafbox<<<(n_entry + 3) / 4, 256, 0, st>>>(n_entry, tb, T, mnode, prm, pp, X);
         RS_HIP(hipGetLastError());
     }
     // internal boxes, deepest level first

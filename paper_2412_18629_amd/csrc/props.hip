@@ -566,7 +566,6 @@ __global__ void k_sd_level0(PrTree T, const int32_t* __restrict__ leafcnt,
 // the kind a hierarchy gives (SD_EXACT), and when an offset took an image
 // shift (SD_SHIFT).
 constexpr int SC_ROWS = 9;
-constexpr float LB_WRAP = 0.0078125f;
 constexpr int SD_EXACT = 1, SD_SHIFT = 2;
 
 struct SeedFrame {
