@@ -64,10 +64,10 @@ FLAGS = {"learned": rs.RS_LEARNED, "batched": rs.RS_BATCHED, "plain": rs.RS_PLAI
 # is only used while these sources are unchanged)
 KERNEL_SYMBOL = {
     # the timed instantiations (32-bit member offsets, no pair counters)
-    "fof3d_link": ("void rs::k_link<true, true, false>(", ["fof3d.hip", "common.h"]),
-    "phase_large_nn": ("void rs::k_tree_nn<true, false>(",
-                       ["phase_tree.hip", "phase_common.h", "common.h"]),
-    "phase_large_link": ("void rs::k_tile_link<true, false>(",
+    "fof3d_link": ("void rs::k_link<true, true, false, false>(", ["fof3d.hip", "common.h"]),
+    "phase_large_nn": ("void rs::k_tile_search<true, true, false>(",
+                       ["phase_tile.hip", "phase_common.h", "common.h"]),
+    "phase_large_link": ("void rs::k_tile_search<false, true, false>(",
                          ["phase_tile.hip", "phase_common.h", "common.h"]),
     "phase_small": ("void rs::k_small_subtree<",
                     ["phase_small.hip", "phase_common.h", "common.h"]),
@@ -100,7 +100,7 @@ def _pmc_rows(path, counter):
 
 def _kernel_values(rows, kernel):
     """Counter values of one timed kernel's dispatches, in dispatch order.  A
-    `k_tree_nn` dispatch that follows the acceptance of the learned brackets
+    `k_tile_search` dispatch that follows the acceptance of the learned brackets
     (`k_laccept`) is the refinement pass, timed as phase_large_nn_fallback and
     left out of phase_large_nn."""
     sym = KERNEL_SYMBOL[kernel][0]

@@ -172,7 +172,50 @@ inline int xcd_chunk(int ntiles) {
 }
 
 int tree_nn(const TArgs& A, int ntiles, float* d2, hipStream_t st);
-int tile_link(const TArgs& A, int ntiles, const float* d2, int32_t* par, hipStream_t st);
+int tile_nn(const TArgs& A, int ntiles, float* d2, hipStream_t st);
+int tile_link(const TArgs& A, int ntiles, float* d2, int32_t* par, hipStream_t st);
+
+// A node's nearest-neighbour search: the cap on d^2, the d^2 that ends a
+// query early, and for the refinements of a rejected bracket which stored
+// values are searched again.
+//   1 bracket: capped just above hi^2, ended by the first neighbour within
+//     lo^2; codes 0 = within lo, the exact d^2 in (lo^2, hi^2], +inf = nothing
+//     within hi
+//   Refinement searches only the queries that can hold the k-th smallest d^2;
+//   every other stored value already orders correctly against it.
+//   3 the queries coded 0, capped just above lo^2, ended by the first
+//     neighbour within lo3 = REFINE_LO2 lo^2 (coded 0 again)
+//   6 those still coded 0, when the k-th value lies within lo3 too: exactly,
+//     capped just above lo3
+//   4 the queries coded +inf, capped at cap4 = REFINE_CAP2 hi^2 (+inf beyond)
+//   5 those still coded +inf, when the k-th value lies beyond cap4 too: no cap
+//   0 exactly, no cap
+struct NNMode {
+    float cap, stop, redo;
+    bool refine;
+};
+
+RS_DEV NNMode nn_mode(const LParam& P) {
+    auto above = [](float v) { return __uint_as_float(__float_as_uint(v) + 1u); };
+    NNMode m;
+    m.cap = P.nnmode == 1   ? above(P.hi2)
+            : P.nnmode == 3 ? above(P.lo2)
+            : P.nnmode == 4 ? above(REFINE_CAP2 * P.hi2)
+            : P.nnmode == 6 ? above(REFINE_LO2 * P.lo2)
+                            : __builtin_huge_valf();
+    m.stop = P.nnmode == 1 ? P.lo2 : P.nnmode == 3 ? REFINE_LO2 * P.lo2 : -1.0f;
+    m.redo = P.nnmode == 3 || P.nnmode == 6 ? 0.0f : __builtin_huge_valf();
+    m.refine = P.nnmode >= 3;
+    return m;
+}
+
+// the stored value of a query whose search found `best`
+RS_DEV float nn_code(const NNMode& m, const LParam& P, float best) {
+    if (P.nnmode == 1) return best <= P.lo2 ? 0.0f : best <= P.hi2 ? best : __builtin_huge_valf();
+    if (P.nnmode == 3 && best <= m.stop) return 0.0f;
+    if (P.nnmode == 4 && !(best <= REFINE_CAP2 * P.hi2)) return __builtin_huge_valf();
+    return best;
+}
 
 
 // device buffers of the large-node pipeline, sized by the level-0 total of

@@ -1,4 +1,5 @@
-// phase_tile.hip -- tile-cooperative linking over the 6D tree.
+// phase_tile.hip -- tile-cooperative searches over the 6D tree: the links
+// within the linking length, and the nearest-neighbour distances.
 //
 // One wavefront owns a tile of 64 consecutive members (one query per lane).
 // It walks the tree ONCE with the bounding box of its queries, collecting
@@ -6,14 +7,22 @@
 // entries per pass: cells average about ten children).  Up to 64 listed
 // leaves at a time, one per lane, are then bounded against every query; each
 // admitted leaf is read once and screened by matrix products against the
-// queries that admit it (see k_tile_link), and the pairs that the screening
-// cannot exclude are evaluated exactly and united, 64 at a time.
+// queries that admit it (see k_tile_search), and the pairs that the screening
+// cannot exclude are evaluated exactly, 64 at a time, and united or taken for
+// the minima.
 //
-// What bounds it: latency (vector unit 40 % busy, matrix cores 20 %), half of
-// it the union-find's dependent reads.  512^3 workload, all levels: 199 -> 138 ms.
-// Deeply nested 9.1M particles 34.2 -> 16 ms (23 ms with the products alone;
-// the rest from ending a pair at equal parents, see unite_pair), 256^3 15.0
-// -> 9.1 ms.  Loading the next leaf's operands ahead measured the same.
+// What bounds it: latency (vector unit 40 % busy, matrix cores 20 %), in the
+// linking half of it the union-find's dependent reads.  All levels of one step,
+// before this kernel and with it:
+//   linking          512^3 199 -> 138 ms, deeply nested 9.1M particles
+//                    34.2 -> 16 ms (23 ms with the products alone; the rest
+//                    from ending a pair at equal parents, see unite_pair),
+//                    256^3 15.0 -> 9.1 ms
+//   nearest (bracketed search) 512^3 237 -> 193 ms, deeply nested 29.7 -> 30.8
+//   nearest (exact) 256^3 36.4 -> 16.5 + 1.1 ms (left to k_tree_nn),
+//                    1M particles 6.5 -> 3.4 + 0.4 ms
+// Loading the next leaf's operands ahead measured the same, as did five to
+// eight wavefronts per SIMD.
 #include "phase_common.h"
 
 namespace rs {
@@ -128,6 +137,18 @@ RS_DEV float xload(const float* __restrict__ base, int64_t i, int off = 0) {
         return base[i + off];
 }
 
+// exact d^2 of two members (the image shift changes nothing where a node has
+// none)
+template <bool O32>
+RS_DEV float exact_d2(const Members& T, int64_t i, int64_t j, const LParam& P,
+                      const PhaseParams& pp) {
+    return phase_d2<true>(mload<O32>(T.x, i), mload<O32>(T.y, i), mload<O32>(T.z, i),
+                          mload<O32>(T.vx, i), mload<O32>(T.vy, i), mload<O32>(T.vz, i),
+                          mload<O32>(T.x, j), mload<O32>(T.y, j), mload<O32>(T.z, j),
+                          mload<O32>(T.vx, j), mload<O32>(T.vy, j), mload<O32>(T.vz, j), P.a,
+                          P.c, pp.L, pp.h);
+}
+
 // Unites the components of a and b, whose parents pa and pb have just been
 // read.  Both walks advance together, and both ends are left pointing at the
 // root they found (a non-root's parent is only ever replaced by an ancestor),
@@ -155,22 +176,32 @@ RS_DEV void unite_pair(int* par, int a, int b, int pa, int pb) {
         __hip_atomic_store(par + b, ra, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Links within l among later members.  One wavefront per tile of 64
-// consecutive members of one node (tiles never straddle nodes).  Pairs found
-// within l are queued in LDS and united 64 at a time, one pair per lane, so
-// that the union-find walks of many pairs are in flight together instead of
-// one or two lanes walking while the rest of the wavefront waits.
 // pair tests of the counting build (instrumentation level 2)
-__device__ unsigned long long g_link_pairs[64];
+__device__ unsigned long long g_link_pairs[64], g_near_pairs[64];
 
-template <bool O32, bool CNT>
+// NN false: links within l among later members; the active queries are those
+// with d_i^2 <= l^2, all with that threshold.
+//
+// NN true: nearest-neighbour d^2 of the tile's members in the modes of
+// k_tree_nn (which explains them and their codes).  A query's threshold is
+// its best d^2 so far, first the nearest in its own tile, and the search cap;
+// it falls as candidates are evaluated, and a query whose best is within the
+// early stop leaves the search.  Without a cap (modes 0 and 5) the tile
+// searches up to the first guess that nine tenths of its queries stay below,
+// as one far outlier would have the whole tile walk the tree; a query with
+// nothing that near is left for k_tree_nn, marked by the negated bound it has
+// (256^3, both kernels: three quarters 19.7 ms, half 25.8, nine tenths 17.7).
+// Nodes that percolate are left to it altogether.
+template <bool NN, bool O32, bool CNT>
 __global__ void __launch_bounds__(64, 6)
-k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
-            int32_t* __restrict__ par) {
+k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
+              int32_t* __restrict__ par) {
     __shared__ TSlot<O32> stk[TSTACK];
     __shared__ int32_t list[TLIST];
     __shared__ int2 hits[THITS];
-    __shared__ float qX[8 * QS];     // -2 X of the queries, 1, scaled norm less the threshold
+    __shared__ float qX[9 * QS];     // -2 X of the queries, 1, scaled norm less the threshold,
+                                     // and the threshold of the box bounds
+    __shared__ uint32_t bst[NN ? 64 : 1];   // best d^2 of the queries, as bits
     __shared__ float tbox[12];       // box of the active queries
     __shared__ int32_t col[16];      // query of each column
     const int lane = threadIdx.x;
@@ -184,16 +215,118 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
     const LParam P = A.prm[v];
     const Members& T = A.T;
     const PhaseParams& pp = A.pp;
-    const float l2 = P.l2;
     const bool cull = P.cull != 0;
+    if (NN && (!cull || P.nnmode == 2)) return;
+    const NNMode md = nn_mode(P);
 
     // this lane's query
     const int64_t mq = ts + lane;
     const bool valid = mq < te;
     const int64_t mm = valid ? mq : ts;
-    const bool act = valid && mload<O32>(d2, mm) <= l2;
-    const uint64_t amask = __ballot(act);
+    const float l2 = P.l2;
+    bool act = valid && (NN ? !md.refine || d2[mm] == md.redo : mload<O32>(d2, mm) <= l2);
+    uint64_t amask = __ballot(act);
     if (!amask) return;
+    const int lm = lane & 15, lk = lane >> 4, lkb = lk < 2 ? lk : 2;
+    // A pair is a candidate when its bound does not exceed the threshold (with
+    // the slack of image shifts where the node has them); the tiny constant
+    // makes the difference negative for coinciding points at threshold 0.
+    const float eta = sqrtf(P.a) * box_slack(pp.L);
+    auto slacked = [&](float r2) {
+        return P.nowrap ? r2
+                        : r2 * (1.0f + LB_WRAP) + (1.0f + 1.0f / LB_WRAP) * 1.001f * eta * eta;
+    };
+    const float norm = xload<O32>(A.X.b, 3 * mm + 2);
+    auto set_threshold = [&](float r2) {
+        const float thr = slacked(r2);
+        qX[7 * QS + lane] = norm - (thr * 1.000001f + 1e-30f);
+        qX[8 * QS + lane] = 4.0f * (thr * 1.00001f + 1e-30f);
+    };
+#pragma unroll
+    for (int k = 0; k < 4; k++) qX[k * QS + lane] = -2.0f * xload<O32>(A.X.a, 4 * mm + k);
+#pragma unroll
+    for (int k = 0; k < 2; k++) qX[(4 + k) * QS + lane] = -2.0f * xload<O32>(A.X.b, 3 * mm + k);
+    qX[6 * QS + lane] = 1.0f;
+    qX[7 * QS + lane] = norm;
+    if (lane < 8) qX[lane * QS + 64] = lane < 6 ? 0.0f : lane == 6 ? 1.0f : NORM_PAD;
+    if (lane < 16) col[lane] = 0;
+    __syncthreads();
+
+    float best = 0.0f;      // NN: nearest d^2 found (or the cap)
+    float r2 = l2;          // largest threshold of the active queries
+    float limit = md.cap;   // NN: distances beyond it are not resolved here
+    if constexpr (NN) {
+        // the nearest in the tile: all its pairs' bounds, then the exact d^2 to
+        // the best bounded (only a first threshold: the tile's leaves are
+        // searched like all others)
+        const int n = (int)(te - ts);
+        const int32_t kmask = key_mask();
+        int32_t k1[4];
+#pragma unroll
+        for (int cb = 0; cb < 4; cb++) k1[cb] = 0x7fffffff;
+        for (int rb = 0; rb < 4; rb++) {
+            const int64_t m = ts + 16 * rb + lm;
+            const float a0 = xload<O32>(A.X.a, 4 * m + lk);
+            float a1 = xload<O32>(A.X.b, 3 * m + lkb);
+            if (lk == 3) a1 = 1.0f;
+#pragma unroll
+            for (int cb = 0; cb < 4; cb++) {
+                f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+                o = mfma_16x16x4(a0, qX[lk * QS + 16 * cb + lm], o);
+                o = mfma_16x16x4(a1, qX[(4 + lk) * QS + 16 * cb + lm], o);
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const int row = 16 * rb + 4 * lk + k;
+                    const float b = row >= n || row == 16 * cb + lm ? NORM_PAD : o[k];
+                    k1[cb] = min(k1[cb], key_of(b, rb << 2 | k, kmask));
+                }
+            }
+        }
+        int near = 0;
+#pragma unroll
+        for (int cb = 0; cb < 4; cb++) {
+            int row = (key_row(k1[cb]) >> 2) * 16 + 4 * lk + (k1[cb] & 3);
+#pragma unroll
+            for (int o = 16; o <= 32; o <<= 1) {
+                const int32_t f = __shfl_xor(k1[cb], o, 64);
+                const int fr = __shfl_xor(row, o, 64);
+                row = f < k1[cb] ? fr : row;
+                k1[cb] = min(k1[cb], f);
+            }
+            if (lk == cb) near = row;
+        }
+        best = md.cap;
+        if (act && n > 1 && near < n && near != lane)
+            best = fminf(best, exact_d2<O32>(T, mm, ts + near, P, pp));
+        act = act && !(best <= md.stop);
+        amask = __ballot(act);
+        if (!(md.cap < __builtin_huge_valf())) {
+            // the bound that nine tenths of the queries stay below
+            const uint32_t bits = __float_as_uint(best);
+            uint64_t cand = amask;
+            int kk = (9 * __popcll(amask) + 9) / 10;
+            for (int b = 30; b >= 0 && __popcll(cand) > 1; b--) {
+                const uint64_t zero = cand & __ballot(((bits >> b) & 1u) == 0);
+                const int c = __popcll(zero);
+                if (kk <= c) cand = zero;
+                else {
+                    kk -= c;
+                    cand &= ~zero;
+                }
+            }
+            if (cand) limit = lane_f(best, __builtin_ctzll(cand));
+            if (!(limit < __builtin_huge_valf())) {   // no guess at all (a lone member)
+                limit = -1.0f;
+                act = false;
+                amask = 0;
+            }
+        }
+        bst[lane] = __float_as_uint(best);
+        set_threshold(fminf(best, limit));
+        r2 = __uint_as_float(~wave_min_u32(act ? ~__float_as_uint(fminf(best, limit)) : ~0u));
+    } else {
+        set_threshold(l2);
+    }
     // its place in the boxes' frame, loaded where it is needed (registers
     // decide how many wavefronts hide each other's latencies here)
     auto load_query = [&](float q[6]) {
@@ -217,47 +350,37 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
             }
         }
     }
-    // a pair is a candidate when its bound does not exceed l^2 (with the slack
-    // of image shifts where the node has them); the tiny constant makes the
-    // difference negative for coinciding points at l = 0
-    const int lm = lane & 15, lk = lane >> 4, lkb = lk < 2 ? lk : 2;
-    float reach, l2x4;
-    {
-        const float eta = sqrtf(P.a) * box_slack(pp.L);
-        const float thr = P.nowrap ? l2 : l2 * (1.0f + LB_WRAP) +
-                                              (1.0f + 1.0f / LB_WRAP) * 1.001f * eta * eta;
-        reach = sqrtf(thr);
-        l2x4 = 4.0f * (thr * 1.00001f + 1e-30f);
-#pragma unroll
-        for (int k = 0; k < 4; k++) qX[k * QS + lane] = -2.0f * xload<O32>(A.X.a, 4 * mm + k);
-#pragma unroll
-        for (int k = 0; k < 2; k++) qX[(4 + k) * QS + lane] = -2.0f * xload<O32>(A.X.b, 3 * mm + k);
-        qX[6 * QS + lane] = 1.0f;
-        qX[7 * QS + lane] = xload<O32>(A.X.b, 3 * mm + 2) - (thr * 1.000001f + 1e-30f);
-        if (lane < 8) qX[lane * QS + 64] = lane < 6 ? 0.0f : lane == 6 ? 1.0f : NORM_PAD;
-        if (lane < 16) col[lane] = 0;
-    }
-    const int64_t first_act = ts + __ffsll((unsigned long long)amask) - 1;
+    const float reach = sqrtf(slacked(r2));
+    const int64_t first_act =
+        NN ? -1 : ts + __ffsll((unsigned long long)amask) - 1;   // later members only
 
     int nhit = 0;
     unsigned long long npairs = 0;   // counting build only
-    auto unite_hits = [&]() {
+    // the queued candidates, one per lane: linked, or taken for the minima
+    auto drain = [&]() {
         __syncthreads();
         if (lane < nhit) {
             const int2 p = hits[lane];
-            const int pa = uf_load(par, p.x), pb = uf_load(par, p.y);
-            if (pa != pb) {   // else one component already
-                const float d = phase_d2<true>(
-                    mload<O32>(T.x, p.x), mload<O32>(T.y, p.x), mload<O32>(T.z, p.x),
-                    mload<O32>(T.vx, p.x), mload<O32>(T.vy, p.x), mload<O32>(T.vz, p.x),
-                    mload<O32>(T.x, p.y), mload<O32>(T.y, p.y), mload<O32>(T.z, p.y),
-                    mload<O32>(T.vx, p.y), mload<O32>(T.vy, p.y), mload<O32>(T.vz, p.y), P.a,
-                    P.c, pp.L, pp.h);
-                if (d <= l2) unite_pair(par, p.x, p.y, pa, pb);
+            if constexpr (NN) {
+                atomicMin(bst + (p.x - (int)ts),
+                          __float_as_uint(exact_d2<O32>(T, p.x, p.y, P, pp)));
+            } else {
+                const int pa = uf_load(par, p.x), pb = uf_load(par, p.y);
+                if (pa != pb && exact_d2<O32>(T, p.x, p.y, P, pp) <= l2)   // else one component
+                    unite_pair(par, p.x, p.y, pa, pb);
             }
         }
         nhit = 0;
         __syncthreads();
+        if constexpr (NN) {
+            const float b = __uint_as_float(bst[lane]);
+            if (b < best) {
+                best = b;
+                set_threshold(fminf(best, limit));
+                act = act && !(best <= md.stop);
+            }
+            amask = __ballot(act);
+        }
     };
 
     // Nodes that percolate (no culling): per buffered leaf, every active query is
@@ -293,7 +416,7 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
                 if (CNT) npairs += (unsigned long long)__popcll(later);
                 const uint64_t hm = later & __builtin_amdgcn_ballot_w64(dd <= l2);
                 if (hm) {
-                    if (nhit + __popcll(hm) > THITS) unite_hits();
+                    if (nhit + __popcll(hm) > THITS) drain();
                     if ((hm >> lane) & 1)
                         hits[nhit + __popcll(hm & lanemask_lt())] =
                             make_int2((int)(ts + src), (int)mj);
@@ -330,6 +453,7 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
             lo[k] = -2.0f * (x1 + e);
             hi[k] = -2.0f * (x0 - e);
         }
+        const float l2x4 = NN ? 0.0f : qX[8 * QS];
         // lane q: the leaves that query q admits.  A step bounds one query
         // against all leaves (some 23 vector instructions, coordinates
         // broadcast from LDS) or one leaf against all queries (some 33, box
@@ -346,7 +470,7 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
                     const float g = p - __builtin_amdgcn_fmed3f(p, lo[k], hi[k]);
                     g2 = fmaf(g, g, g2);
                 }
-                const uint64_t m = __ballot(in && g2 <= l2x4);
+                const uint64_t m = __ballot(in && g2 <= (NN ? qX[8 * QS + q] : l2x4));
                 adm |= m;
                 if (lane == q) {
                     glo = (uint32_t)m;
@@ -365,7 +489,7 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
                         p[k] - __builtin_amdgcn_fmed3f(p[k], lane_f(lo[k], j), lane_f(hi[k], j));
                     g2 = fmaf(g, g, g2);
                 }
-                const bool need = act && g2 <= l2x4;
+                const bool need = act && g2 <= (NN ? qX[8 * QS + lane] : l2x4);
                 adm |= __ballot(need) ? 1ull << j : 0ull;
                 if (j < 32) glo |= need ? 1u << j : 0u;
                 else ghi |= need ? 1u << (j - 32) : 0u;
@@ -377,7 +501,17 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
             adm &= adm - 1;
             const int32_t start = __builtin_amdgcn_readlane(rstart, src);
             const int32_t len = __builtin_amdgcn_readlane(rend, src) - start;
-            const uint64_t mk = __ballot(((src < 32 ? glo : ghi) >> (src & 31)) & 1u);
+            const uint64_t mk =
+                __ballot(((src < 32 ? glo : ghi) >> (src & 31)) & 1u) & (NN ? amask : ~0ull);
+            if (NN && !mk) continue;
+            // members of this tile (or, linking, before it) among the leaf's
+            const bool own = start < (int32_t)te && (!NN || start + len > (int32_t)ts);
+            if (CNT) {
+                const int32_t later = !((mk >> lane) & 1) ? 0
+                    : NN ? len : max(start + len - (int32_t)max((int64_t)start, mq + 1), 0);
+                npairs += (unsigned long long)wave_sum_i32(later);
+            }
+            const int nq = __popcll(mk);
             // all four row blocks, whatever the leaf's length (rows past its end
             // are masked below): no branches between the products
             const int64_t m = (int64_t)start + lm;
@@ -387,17 +521,10 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
                 a0[rb] = xload<O32>(A.X.a, 4 * m + lk, 64 * rb);
                 a1[rb] = xload<O32>(A.X.b, 3 * m + lkb, 48 * rb);
             }
-            const bool own = start < (int32_t)te;   // members of this tile or before it
-            if (CNT) {
-                const int32_t later = (mk >> lane) & 1
-                    ? max(start + len - (int32_t)max((int64_t)start, mq + 1), 0) : 0;
-                npairs += (unsigned long long)wave_sum_i32(later);
-            }
             // results 4 rb + t of a lane, the first in bit 15, are rows
             // 16 rb + 4 lk + t
             const uint32_t rows =
                 (0xffff0000u >> (4 * (len >> 4) + min(max((len & 15) - 4 * lk, 0), 4))) & 0xffffu;
-            const int nq = __popcll(mk);
             const int rank0 = __popcll(mk & lanemask_lt());
 #pragma unroll
             for (int rb = 0; rb < 4; rb++) a1[rb] = lk == 3 ? 1.0f : a1[rb];
@@ -427,9 +554,9 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
                     const int b = 16 - __ffs((int)bits);
                     const int32_t i = (int32_t)ts + q;
                     const int32_t j = start + 16 * (b >> 2) + 4 * lk + (b & 3);
-                    const bool ok = bits != 0 && (!own || j > i);
+                    const bool ok = bits != 0 && (!own || (NN ? j != i : j > i));
                     const uint64_t hm = __ballot(ok);
-                    if (nhit + __popcll(hm) > THITS) unite_hits();
+                    if (nhit + __popcll(hm) > THITS) drain();
                     if (ok) hits[nhit + __popcll(hm & lanemask_lt())] = make_int2(i, j);
                     nhit += __popcll(hm);
                     bits &= bits - 1;
@@ -441,8 +568,15 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
     auto process = [&](int n) {
         if (n == 0) return;   // nothing listed: no entry to read
         __syncthreads();
-        if (cull) screen(n);
-        else replay(n);
+        if constexpr (NN) {
+            screen(n);
+            if (nhit) drain();
+            r2 = __uint_as_float(
+                ~wave_min_u32(act ? ~__float_as_uint(fminf(best, limit)) : ~0u));
+        } else {
+            if (cull) screen(n);
+            else replay(n);
+        }
     };
 
     // walk the tree with the tile box; buffer leaves, flush when full
@@ -451,7 +585,7 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
     TStackEnt se{tb.cfirst[A.root[v]], tb.ccount[A.root[v]]};
     int sp = 0;
     __syncthreads();
-    for (;;) {
+    while (!NN || amask) {
         // cells average about ten children: up to four entries whose
         // children fit in 64 lanes are scanned in one pass, each on its own
         // run of lanes (a pass pushes at most 64 entries, as one cell does)
@@ -505,7 +639,7 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
                     bhi[d] = tbox[6 + d];
                 }
                 need = r.end > first_act + 1 &&
-                       (!cull || !(box_box_lb(blo, bhi, r, P.a, P.c) > l2));
+                       (!cull || !(box_box_lb(blo, bhi, r, P.a, P.c) > r2));
             }
             const uint64_t imask = __ballot(need && !leaf);
             if (need && !leaf)
@@ -529,11 +663,21 @@ k_tile_link(TArgs A, int ntiles, int chunk, const float* __restrict__ d2,
         se = stk[--sp].unpack(tb.erec);
     }
     process(nlist);
-    unite_hits();
-    if (CNT && lane == 0 && npairs) atomicAdd(&g_link_pairs[blockIdx.x & 63], npairs);
+    if constexpr (NN) {
+        if (valid && (!md.refine || d2[mm] == md.redo))
+            d2[mm] = best <= limit ? nn_code(md, P, best) : md.cap < __builtin_huge_valf()
+                                         ? __builtin_huge_valf() : -best;
+        if (CNT && lane == 0 && npairs) atomicAdd(&g_near_pairs[blockIdx.x & 63], npairs);
+    } else {
+        drain();
+        if (CNT && lane == 0 && npairs) atomicAdd(&g_link_pairs[blockIdx.x & 63], npairs);
+    }
 }
 
-int tile_link(const TArgs& A, int ntiles, const float* d2, int32_t* par, hipStream_t st) {
+// Runs one search over the level's tiles; the counting build clears its
+// counters before and reads them back after (synchronous).
+template <bool NN>
+static int tile_search(const TArgs& A, int ntiles, float* d2, int32_t* par, hipStream_t st) {
     if (ntiles <= 0) return RS_OK;
     const int c = xcd_chunk(ntiles);
     // 32-bit offsets: four floats a member in the widest rows, and compact stack
@@ -541,25 +685,33 @@ int tile_link(const TArgs& A, int ntiles, const float* d2, int32_t* par, hipStre
     const bool o32 = use_o32(4 * A.nmem) && A.tb.cap_entry < (1 << 26);
     const unsigned grid = xcd_chunk_grid(ntiles, c);
     if (!prof_count_pairs()) {
-        if (o32) k_tile_link<true, false><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
-        else k_tile_link<false, false><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
+        if (o32) k_tile_search<NN, true, false><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
+        else k_tile_search<NN, false, false><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
         RS_HIP(hipGetLastError());
         return RS_OK;
     }
-    // counting build: counters cleared before, read back after (synchronous)
     unsigned long long h[64] = {0};
     RS_HIP(hipStreamSynchronize(st));
-    RS_HIP(hipMemcpyToSymbol(HIP_SYMBOL(g_link_pairs), h, sizeof(h)));
-    if (o32) k_tile_link<true, true><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
-    else k_tile_link<false, true><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
+    RS_HIP(NN ? hipMemcpyToSymbol(HIP_SYMBOL(g_near_pairs), h, sizeof(h))
+              : hipMemcpyToSymbol(HIP_SYMBOL(g_link_pairs), h, sizeof(h)));
+    if (o32) k_tile_search<NN, true, true><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
+    else k_tile_search<NN, false, true><<<grid, 64, 0, st>>>(A, ntiles, c, d2, par);
     RS_HIP(hipGetLastError());
-    RS_HIP(hipMemcpyFromSymbolAsync(h, HIP_SYMBOL(g_link_pairs), sizeof(h), 0,
-                                    hipMemcpyDeviceToHost, st));
     RS_HIP(hipStreamSynchronize(st));
+    RS_HIP(NN ? hipMemcpyFromSymbol(h, HIP_SYMBOL(g_near_pairs), sizeof(h))
+              : hipMemcpyFromSymbol(h, HIP_SYMBOL(g_link_pairs), sizeof(h)));
     double sum = 0.0;
     for (int i = 0; i < 64; i++) sum += (double)h[i];
-    prof_add_count("pairs_link", sum);
+    prof_add_count(NN ? "pairs_nn" : "pairs_link", sum);
     return RS_OK;
+}
+
+int tile_nn(const TArgs& A, int ntiles, float* d2, hipStream_t st) {
+    return tile_search<true>(A, ntiles, d2, nullptr, st);
+}
+
+int tile_link(const TArgs& A, int ntiles, float* d2, int32_t* par, hipStream_t st) {
+    return tile_search<false>(A, ntiles, d2, par, st);
 }
 
 }  // namespace rs

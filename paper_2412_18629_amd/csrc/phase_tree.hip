@@ -1,5 +1,5 @@
 // phase_tree.hip -- 6D search tree over the Morton-sorted members of the
-// large nodes of one level, and the nearest-neighbour / linking traversals.
+// large nodes of one level, and its search one query at a time.
 //
 // Tree: an internal node is a Morton-prefix cell (6 key bits per level, one
 // per dimension) with more than 64 members.  Its children are the non-empty
@@ -400,10 +400,13 @@ RS_DEV StackEnt stack_unpack(StackSlot s) {
     return StackEnt{s.cfirst, (int32_t)(s.pk & 63u) + 1, __uint_as_float(s.pk & ~63u)};
 }
 
-// nearest-neighbour d^2 of every member (exact): own leaf first, then a
+// nearest-neighbour d^2 (exact) of the members that k_tile_search has left,
+// and of all members of nodes that percolate: own leaf first, then a
 // depth-first descent from the node's root.  One wavefront per tile of
 // queries, one query at a time; child records are bounded lane-parallel,
-// surviving leaves are scanned four at a time with independent loads.
+// surviving leaves are scanned four at a time with independent loads.  This
+// is the better search for a query whose reach is far beyond its tile's, and
+// the worse one for a tile's queries together (see k_tile_search).
 // pair tests of the counting build (instrumentation level 2), spread over 64
 // counters to keep the atomics apart
 __device__ unsigned long long g_nn_pairs[64];
@@ -424,41 +427,24 @@ k_tree_nn(TArgs A, int ntiles, int chunk, float* __restrict__ d2out) {
     const int64_t te = min(ts + 64, nd.t_off + (int64_t)nd.size);
     const bool cull = P.cull != 0;
     if (P.nnmode == 2) return;               // bracket already accepted
-    // bracket mode (1): searches are capped at hi^2 and stop at the first
-    // neighbour within lo^2; the output encodes 0 = within lo, the exact d^2
-    // in (lo^2, hi^2], +inf = nothing within hi.
-    // Refinement after a rejected bracket searches only the queries that can
-    // hold the k-th smallest d^2; every other stored value already orders
-    // correctly against it.  Below lo^2: mode 3 searches the queries coded 0
-    // (capped just above lo^2) with a stop at the first neighbour within
-    // lo3 = REFINE_LO2 lo^2, coding 0 again there and the exact d^2 above;
-    // mode 6, when the k-th value lies within lo3 too, searches the queries
-    // still coded 0 exactly, capped just above lo3.  Above hi^2: mode 4
-    // searches the queries coded +inf capped at cap4 = REFINE_CAP2 hi^2
-    // (+inf beyond it); mode 5, when the k-th value lies beyond cap4 too,
-    // searches the queries still coded +inf without a cap.
-    const int mode = P.nnmode;
-    const bool brk = mode == 1;
-    const float cap4 = REFINE_CAP2 * P.hi2;
-    const float lo3 = REFINE_LO2 * P.lo2;
-    auto above = [](float v) { return __uint_as_float(__float_as_uint(v) + 1u); };
-    const float cap = brk ? above(P.hi2)
-                    : mode == 3 ? above(P.lo2)
-                    : mode == 4 ? above(cap4)
-                    : mode == 6 ? above(lo3)
-                                : __builtin_huge_valf();
-    // early stop: the first neighbour within this d^2 ends a query
-    const float lo2 = brk ? P.lo2 : mode == 3 ? lo3 : -1.0f;
-    const float redo = mode == 3 || mode == 6 ? 0.0f : __builtin_huge_valf();
-    const bool refine = mode >= 3;
+    const NNMode md = nn_mode(P);
+    const float lo2 = md.stop;
+    // the queries this pass is for: where nodes are culled those that the
+    // tile search has left, with the bound it found, else the mode's
+    const int64_t mine = ts + lane < te ? ts + lane : ts;
+    const float stored = cull || md.refine ? d2out[mine] : 0.0f;
+    uint64_t todo = __ballot(ts + lane < te && (cull ? __float_as_int(stored) < 0
+                                                     : !md.refine || stored == md.redo));
     const int32_t rf = tb.cfirst[A.root[v]], rn = tb.ccount[A.root[v]];
     unsigned long long npairs = 0;   // counting build only
-    for (int64_t qm = ts; qm < te; qm++) {
-        if (refine && !(d2out[qm] == redo)) continue;
+    while (todo) {
+        const int ql = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int64_t qm = ts + ql;
         const TQuery q = tq_load(T, qm, P, A.pp);
         const int32_t e0 = tb.leaf_of[qm];
         const int32_t* r0 = reinterpret_cast<const int32_t*>(tb.erec + 16 * (int64_t)e0);
-        float bl = cap;
+        float bl = cull ? -lane_f(stored, ql) : md.cap;
         {
             const int64_t m = r0[12] + lane;
             if (m < r0[13] && m != qm) bl = fminf(bl, tq_d2<O32>(T, m, q, P, A.pp));
@@ -596,11 +582,7 @@ k_tree_nn(TArgs A, int ntiles, int chunk, float* __restrict__ d2out) {
             }
         }
         if (lane == 0) {
-            float out = best;
-            if (brk) out = best <= lo2 ? 0.0f : (best <= P.hi2 ? best : __builtin_huge_valf());
-            else if (mode == 3 && best <= lo3) out = 0.0f;
-            else if (mode == 4 && !(best <= cap4)) out = __builtin_huge_valf();
-            d2out[qm] = out;
+            d2out[qm] = nn_code(md, P, best);
         }
     }
     if (CNT && lane == 0 && npairs) atomicAdd(&g_nn_pairs[blockIdx.x & 63], npairs);
@@ -692,6 +674,7 @@ int tree_refit_active(TreeBuf& tb, int32_t n_entry, const std::vector<int32_t>& 
 }
 
 int tree_nn(const TArgs& A, int ntiles, float* d2, hipStream_t st) {
+    RS_TRY(tile_nn(A, ntiles, d2, st));
     const int c = xcd_chunk(ntiles);
     const bool o32 = use_o32(A.nmem);
     if (!prof_count_pairs()) {
