@@ -11,16 +11,14 @@
 // cannot exclude are evaluated exactly, 64 at a time, and united or taken for
 // the minima.
 //
-// What bounds it: latency (vector unit 40 % busy, matrix cores 20 %), in the
-// linking half of it the union-find's dependent reads.  All levels of one step,
-// before this kernel and with it:
-//   linking          512^3 199 -> 138 ms, deeply nested 9.1M particles
-//                    34.2 -> 16 ms (23 ms with the products alone; the rest
-//                    from ending a pair at equal parents, see unite_pair),
-//                    256^3 15.0 -> 9.1 ms
-//   nearest (bracketed search) 512^3 237 -> 193 ms, deeply nested 29.7 -> 30.8
-//   nearest (exact) 256^3 36.4 -> 16.5 + 1.1 ms (left to k_tree_nn),
-//                    1M particles 6.5 -> 3.4 + 0.4 ms
+// What bounds it: vector instructions (72 % of the issue slots in the
+// nearest-neighbour search), and in the linking also the union-find's
+// dependent reads.  All levels of one step, before this kernel and with it:
+//   linking          512^3 199 -> 117 ms, deeply nested 9.1M particles
+//                    34.2 -> 14.3 ms, 256^3 15.0 -> 8.1 ms
+//   nearest (bracketed search) 512^3 237 -> 145 ms, deeply nested 29.7 -> 27.3
+//   nearest (exact) 256^3 36.4 -> 13.7 + 1.1 ms (left to k_tree_nn),
+//                    1M particles 6.5 -> 3.3 + 0.4 ms
 // Loading the next leaf's operands ahead measured the same, as did five to
 // eight wavefronts per SIMD.
 #include "phase_common.h"
@@ -34,6 +32,13 @@ constexpr int TSTACK = 520;   // >= 64 internal children x 8 levels
 constexpr int TLIST = 128;    // candidate leaves buffered (up to 63, and one pass)
 constexpr int THITS = 64;     // linked pairs buffered before their unions (>= 64)
 static_assert(TLIST >= 127 && THITS == 64, "one pass adds up to 64 leaves or pairs");
+// A leaf that at most FEW queries admit is screened with one member per lane, a
+// query at a time (some 20 vector instructions), instead of in a 16-wide tile
+// that would be mostly empty columns (some 160 with its 32 products).  Two
+// thirds of the leaves are such in 512^3 particles, nearly all of them with
+// more than 32 members.  512^3, nearest and linking: none 193 + 140 ms, up to
+// 2 queries 154 + 123, 4 146 + 118, 6 145 + 117, 9 144 + 117, 14 145 + 119.
+constexpr int FEW = 6;
 constexpr int QS = 68;        // row stride of the queries' coordinates
 
 struct TileRec {
@@ -512,6 +517,31 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
                 npairs += (unsigned long long)wave_sum_i32(later);
             }
             const int nq = __popcll(mk);
+            if (nq <= FEW) {
+                // the same bound, summed in the vector unit
+                const int64_t m = (int64_t)start + lane;
+                float x[7];
+#pragma unroll
+                for (int k = 0; k < 4; k++) x[k] = xload<O32>(A.X.a, 4 * m + k);
+#pragma unroll
+                for (int k = 0; k < 3; k++) x[4 + k] = xload<O32>(A.X.b, 3 * m + k);
+                const int32_t j = start + lane;
+                for (uint64_t left = mk; left; left &= left - 1) {
+                    const int q = __builtin_ctzll(left);
+                    float s = qX[7 * QS + q] + x[6];
+#pragma unroll
+                    for (int k = 0; k < 6; k++) s = fmaf(x[k], qX[k * QS + q], s);
+                    const int32_t i = (int32_t)ts + q;
+                    const bool ok = lane < len && __float_as_int(s) < 0 &&
+                                    (!own || (NN ? j != i : j > i));
+                    const uint64_t hm = __ballot(ok);
+                    if (!hm) continue;
+                    if (nhit + __popcll(hm) > THITS) drain();
+                    if (ok) hits[nhit + __popcll(hm & lanemask_lt())] = make_int2(i, j);
+                    nhit += __popcll(hm);
+                }
+                continue;
+            }
             // all four row blocks, whatever the leaf's length (rows past its end
             // are masked below): no branches between the products
             const int64_t m = (int64_t)start + lm;
