@@ -16,8 +16,8 @@
 // dependent reads.  All levels of one step, before this kernel and with it:
 //   linking          512^3 199 -> 117 ms, deeply nested 9.1M particles
 //                    34.2 -> 14.3 ms, 256^3 15.0 -> 8.1 ms
-//   nearest (bracketed search) 512^3 237 -> 145 ms, deeply nested 29.7 -> 27.3
-//   nearest (exact) 256^3 36.4 -> 13.7 + 1.1 ms (left to k_tree_nn),
+//   nearest (bracketed search) 512^3 237 -> 135 ms, deeply nested 29.7 -> 26.7
+//   nearest (exact) 256^3 36.4 -> 13.1 + 1.1 ms (left to k_tree_nn),
 //                    1M particles 6.5 -> 3.3 + 0.4 ms
 // Loading the next leaf's operands ahead measured the same, as did five to
 // eight wavefronts per SIMD.
@@ -672,9 +672,17 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
                        (!cull || !(box_box_lb(blo, bhi, r, P.a, P.c) > r2));
             }
             const uint64_t imask = __ballot(need && !leaf);
-            if (need && !leaf)
-                stk[sp + __popcll(imask & lanemask_lt())] =
-                    TSlot<O32>::pack(k, r.cfirst, r.ccount);
+            // nearest first: the cell that holds the tile goes on top, so that its
+            // neighbourhood is searched before what is further up the tree (512^3
+            // 143 -> 135 ms; boxes of the queries still active, taken anew, cost
+            // more than they save)
+            int at = sp + __popcll(imask & lanemask_lt());
+            if constexpr (NN) {
+                const bool top = need && !leaf && r.start <= (int32_t)ts && (int32_t)ts < r.end;
+                const uint64_t tm = __ballot(top);
+                if (tm) at = top ? sp + __popcll(imask) - 1 : at - (int)((tm & lanemask_lt()) != 0);
+            }
+            if (need && !leaf) stk[at] = TSlot<O32>::pack(k, r.cfirst, r.ccount);
             sp += __popcll(imask);
             const uint64_t lmask = __ballot(need && leaf);
             if (need && leaf) list[nlist + __popcll(lmask & lanemask_lt())] = k;
