@@ -90,39 +90,53 @@ __global__ void k_p_interleave(int64_t n, const float* __restrict__ x, const flo
     rec[3 * i + 2] = make_float2(vy[i], vz[i]);
 }
 
-// members packed per group in ascending particle index (the sort is stable)
+// Members packed per group in ascending particle index (the sort is stable).
+// Bound by the lines of the gathered records, so a record is read as two loads
+// (16 and 8 bytes) and nothing is scattered here (134M members: 9.9 ms with
+// three loads and the scatter that k_p_deepest replaces -> 4.5 + 0.7 ms).
 __global__ void k_p_fill(int64_t n, const float2* __restrict__ rec,
                          const int32_t* __restrict__ sidx, const int32_t* __restrict__ flag,
                          const int32_t* __restrict__ rex, const int32_t* __restrict__ rstart,
-                         const int32_t* __restrict__ keep, const int32_t* __restrict__ gid,
-                         const int32_t* __restrict__ goff, Members A,
-                         int32_t* __restrict__ deepest) {
+                         const int32_t* __restrict__ keep, const int32_t* __restrict__ goff,
+                         Members A) {
+    struct alignas(8) Rec { float v[6]; };
     int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (p >= n) return;
     int32_t r = rex[p] + flag[p] - 1;
+    if (!keep[r]) return;
     int32_t i = sidx[p];
-    if (!keep[r]) {
-        deepest[i] = -1;
-        return;
-    }
     int64_t pos = (int64_t)goff[r] + (p - rstart[r]);
-    const float2 a = rec[3 * (int64_t)i], b = rec[3 * (int64_t)i + 1], c = rec[3 * (int64_t)i + 2];
-    A.x[pos] = a.x;
-    A.y[pos] = a.y;
-    A.z[pos] = b.x;
-    A.vx[pos] = b.y;
-    A.vy[pos] = c.x;
-    A.vz[pos] = c.y;
+    const Rec q = reinterpret_cast<const Rec*>(rec)[i];
+    A.x[pos] = q.v[0];
+    A.y[pos] = q.v[1];
+    A.z[pos] = q.v[2];
+    A.vx[pos] = q.v[3];
+    A.vy[pos] = q.v[4];
+    A.vz[pos] = q.v[5];
     A.idx[pos] = i;
-    deepest[i] = gid[r];
+}
+
+// a particle's level-0 group from its label: gmap is the group of a kept
+// label, -1 elsewhere.  In particle order, so that the writes are whole lines
+// and the few kept labels' entries stay in the caches; written from the packed
+// order it cost a 64-byte line a particle.
+__global__ void k_p_deepest(int64_t n, const int32_t* __restrict__ lab,
+                            const int32_t* __restrict__ gmap, int32_t* __restrict__ deepest) {
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < n) deepest[i] = gmap[lab[i]];
 }
 
 // Percolation of each 3D group: per axis the smallest and largest integer
 // displacement of its members from the reference member (the first packed
 // member, the smallest index), in the nearest periodic image exactly as for
 // the dispersions.  Stored offset by 2^62 so that unsigned atomics order
-// them; lanes of one group (members are packed per group) combine first.
+// them.  A wavefront goes through SPAN_ROWS rows of 64 members and reduces a
+// group's extremes once, where the group ends or its rows do (members are
+// packed per group): with a reduction and six atomics a row, the atomics on
+// large groups' extremes set the time (134M members 10.5 -> 1.6 ms beside the
+// small groups' kernels, deeply nested 9.1M 4.4 -> 0.3 ms).
 constexpr unsigned long long SPAN_OFF = 1ull << 62;
+constexpr int SPAN_ROWS = 16;
 
 __global__ void k_p_span_init(int32_t G, unsigned long long* __restrict__ span) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -134,39 +148,66 @@ __global__ void k_p_span(int64_t n, const int32_t* __restrict__ flag,
                          const int32_t* __restrict__ keep, const int32_t* __restrict__ gid,
                          const int32_t* __restrict__ goff, Members A, int64_t LQ,
                          unsigned long long* __restrict__ span) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    bool ok = p < n;
-    const int32_t r = ok ? rex[p] + flag[p] - 1 : 0;
-    ok = ok && keep[r];
-    const int32_t g = ok ? gid[r] : -1;
-    unsigned long long d[3] = {SPAN_OFF, SPAN_OFF, SPAN_OFF};
-    if (ok) {
-        const int64_t ref = goff[r], pos = ref + (p - rstart[r]);
-        const float* ax3[3] = {A.x, A.y, A.z};
+    const int lane = threadIdx.x & 63;
+    const int64_t w = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6);
+    const float* ax3[3] = {A.x, A.y, A.z};
+    int32_t cg = -1;   // the group being gathered, the same in all lanes
+    unsigned long long mn[3], mx[3];
+    auto flush = [&]() {
+        if (cg < 0) return;
 #pragma unroll
         for (int ax = 0; ax < 3; ax++) {
-            int64_t q = quant_pos(ax3[ax][pos]) - quant_pos(ax3[ax][ref]);
-            if (2 * q > LQ) q -= LQ;
-            else if (2 * q <= -LQ) q += LQ;
-            d[ax] = (unsigned long long)(q + (int64_t)SPAN_OFF);
-        }
-    }
-    uint64_t todo = __ballot(ok);
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int32_t lg = __shfl(g, leader, 64);
-        const bool mine = ok && g == lg;
-#pragma unroll
-        for (int ax = 0; ax < 3; ax++) {
-            const unsigned long long mn = wave_min_u64(mine ? d[ax] : ~0ull);
-            const unsigned long long mx = ~wave_min_u64(mine ? ~d[ax] : ~0ull);
-            if ((int)(threadIdx.x & 63) == leader) {
-                atomicMin(span + 6 * (int64_t)lg + ax, mn);
-                atomicMax(span + 6 * (int64_t)lg + 3 + ax, mx);
+            const unsigned long long lo = wave_min_u64(mn[ax]), hi = ~wave_min_u64(~mx[ax]);
+            unsigned long long* s = span + 6 * (int64_t)cg + ax;
+            // a stale value is never the better one
+            if (lane == 0) {
+                if (lo < s[0]) atomicMin(s, lo);
+                if (hi > s[3]) atomicMax(s + 3, hi);
             }
         }
-        todo &= ~__ballot(mine);
+    };
+    for (int row = 0; row < SPAN_ROWS; row++) {
+        const int64_t p = (w * SPAN_ROWS + row) * 64 + lane;
+        bool ok = p < n;
+        const int32_t r = ok ? rex[p] + flag[p] - 1 : 0;
+        ok = ok && keep[r];
+        uint64_t todo = __ballot(ok);
+        if (!todo) continue;
+        const int32_t g = ok ? gid[r] : -1;
+        unsigned long long d[3] = {SPAN_OFF, SPAN_OFF, SPAN_OFF};
+        if (ok) {
+            const int64_t ref = goff[r], pos = ref + (p - rstart[r]);
+#pragma unroll
+            for (int ax = 0; ax < 3; ax++) {
+                int64_t q = quant_pos(ax3[ax][pos]) - quant_pos(ax3[ax][ref]);
+                if (2 * q > LQ) q -= LQ;
+                else if (2 * q <= -LQ) q += LQ;
+                d[ax] = (unsigned long long)(q + (int64_t)SPAN_OFF);
+            }
+        }
+        while (todo) {
+            const int32_t lg = __builtin_amdgcn_readlane(g, __builtin_ctzll(todo));
+            const bool mine = ok && g == lg;
+            if (lg != cg) {
+                flush();
+                cg = lg;
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) {
+                    mn[ax] = ~0ull;
+                    mx[ax] = 0ull;
+                }
+            }
+            if (mine) {
+#pragma unroll
+                for (int ax = 0; ax < 3; ax++) {
+                    mn[ax] = d[ax] < mn[ax] ? d[ax] : mn[ax];
+                    mx[ax] = d[ax] > mx[ax] ? d[ax] : mx[ax];
+                }
+            }
+            todo &= ~__ballot(mine);
+        }
     }
+    flush();
 }
 
 // a group percolates when on some axis 2 * (max - min) >= L_Q
@@ -188,12 +229,14 @@ __global__ void k_p_class(int32_t nruns, const int32_t* __restrict__ rstart,
                           const int32_t* __restrict__ goff, const int32_t* __restrict__ sidx,
                           NodeRec nr, SmallItem* __restrict__ buckets, int64_t stride,
                           int32_t* __restrict__ bcount, ChildOut* __restrict__ large,
-                          int32_t* __restrict__ nlarge) {
+                          int32_t* __restrict__ nlarge, const int32_t* __restrict__ lab,
+                          int32_t* __restrict__ gmap) {
     int32_t r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= nruns || !keep[r]) return;
     int32_t g = gid[r];
     int32_t sz = rstart[r + 1] - rstart[r];
     int32_t mi = sidx[rstart[r]];
+    gmap[lab[mi]] = g;
     nr.level[g] = 0;
     nr.minidx[g] = mi;
     nr.parent[g] = -1;
@@ -411,17 +454,20 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
         *overflow = true;
         return RS_OK;
     }
-    k_p_fill<<<gb, BT, 0, st>>>(n, prec, sidx, flag, rex, rstart, keep, gid, goff, A, deepest);
+    int32_t* gmap = klen;   // the run lengths have been scanned
+    k_p_fill<<<gb, BT, 0, st>>>(n, prec, sidx, flag, rex, rstart, keep, goff, A);
+    RS_TRY(fill_i32(gmap, -1, n, st));
     k_p_class<<<grid_for(nruns, BT, 1ll << 31), BT, 0, st>>>(nruns, rstart, keep, gid, goff, sidx,
                                                               nr, buckets, bstride, ctr + 8,
-                                                              large0, ctr + 12);
+                                                              large0, ctr + 12, lab, gmap);
+    k_p_deepest<<<gb, BT, 0, st>>>(n, lab, gmap, deepest);
     RS_HIP(hipGetLastError());
     // percolation flags of the groups; only the output reads them, so the
     // batched form runs them on the side stream of the level-0 subtrees
     auto span_pass = [&](hipStream_t s) {
         if (G <= 0) return;
         k_p_span_init<<<grid_for(6 * (int64_t)G, BT, 1ll << 31), BT, 0, s>>>(G, gspan);
-        k_p_span<<<gb, BT, 0, s>>>(n, flag, rex, rstart, keep, gid, goff, A, pp.LQ, gspan);
+        k_p_span<<<grid_for((n + SPAN_ROWS - 1) / SPAN_ROWS, BT, 1ll << 31), BT, 0, s>>>(n, flag, rex, rstart, keep, gid, goff, A, pp.LQ, gspan);
         k_p_wide<<<grid_for(G, BT, 1ll << 31), BT, 0, s>>>(G, gspan, pp.LQ, wide0);
     };
     RS_TRY(fill_i32(nr.count, G, 1, st));
