@@ -330,7 +330,10 @@ int tune_get(TuneKnob k);
 size_t scan_temp_bytes(int64_t n);
 int scan_exclusive_i32(const int32_t* in, int32_t* out, int64_t n, void* temp,
                        int32_t* total_dev, hipStream_t st);
-size_t sort_temp_bytes(int64_t n);
+size_t sort_temp_bytes(int64_t n, size_t key_bytes = 8);
+int sort_pairs_u32_i32(const uint32_t* kin, uint32_t* kout, const int32_t* vin,
+                       int32_t* vout, int64_t n, int bits, void* temp, size_t temp_bytes,
+                       hipStream_t st);
 int sort_pairs_u64_i32(const uint64_t* kin, uint64_t* kout, const int32_t* vin,
                        int32_t* vout, int64_t n, int bits, void* temp, size_t temp_bytes,
                        hipStream_t st);

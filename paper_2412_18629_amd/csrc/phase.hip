@@ -30,13 +30,16 @@ namespace rs {
 // level 0
 // ---------------------------------------------------------------------------
 
-// validation + sort keys: (label, index) pairs
+// validation, sort keys ((label, index) pairs), and the six phase-space
+// coordinates of every particle interleaved, 24 bytes a particle, so that the
+// gather of k_p_fill fetches one record (one or two cache lines) per member
+// instead of six scattered values
 __global__ void k_p_keys(const float* __restrict__ x, const float* __restrict__ y,
                          const float* __restrict__ z, const float* __restrict__ vx,
                          const float* __restrict__ vy, const float* __restrict__ vz,
                          const int32_t* __restrict__ lab, int64_t n, float L,
-                         uint64_t* __restrict__ keys, int32_t* __restrict__ vals,
-                         int32_t* __restrict__ err) {
+                         uint32_t* __restrict__ keys, int32_t* __restrict__ vals,
+                         float2* __restrict__ rec, int32_t* __restrict__ err) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     bool bad = !(x[i] >= 0.0f && x[i] < L) || !(y[i] >= 0.0f && y[i] < L) ||
@@ -49,12 +52,15 @@ __global__ void k_p_keys(const float* __restrict__ x, const float* __restrict__ 
         atomicOr(err, 2);
         l = 0;
     }
-    keys[i] = (uint64_t)(uint32_t)l;
+    keys[i] = (uint32_t)l;
     vals[i] = (int32_t)i;
+    rec[3 * i] = make_float2(x[i], y[i]);
+    rec[3 * i + 1] = make_float2(z[i], vx[i]);
+    rec[3 * i + 2] = make_float2(vy[i], vz[i]);
 }
 
 // run starts of equal labels in the sorted order
-__global__ void k_p_runflag(int64_t n, const uint64_t* __restrict__ slab,
+__global__ void k_p_runflag(int64_t n, const uint32_t* __restrict__ slab,
                             int32_t* __restrict__ flag) {
     int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (p < n) flag[p] = (p == 0 || slab[p] != slab[p - 1]) ? 1 : 0;
@@ -74,20 +80,6 @@ __global__ void k_p_keep(int32_t nruns, const int32_t* __restrict__ rstart, int3
     bool k = len >= min_group;
     keep[r] = k ? 1 : 0;
     klen[r] = k ? len : 0;
-}
-
-// the six phase-space coordinates of every particle interleaved, 24 bytes a
-// particle, so that the gather below fetches one record (one or two cache
-// lines) per member instead of six scattered values
-__global__ void k_p_interleave(int64_t n, const float* __restrict__ x, const float* __restrict__ y,
-                               const float* __restrict__ z, const float* __restrict__ vx,
-                               const float* __restrict__ vy, const float* __restrict__ vz,
-                               float2* __restrict__ rec) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    rec[3 * i] = make_float2(x[i], y[i]);
-    rec[3 * i + 1] = make_float2(z[i], vx[i]);
-    rec[3 * i + 2] = make_float2(vy[i], vz[i]);
 }
 
 // Members packed per group in ascending particle index (the sort is stable).
@@ -352,8 +344,7 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
     // ---- arena 1: level-0 tables, records, output sort ----
     size_t bytes = 0;
     auto add = [&](size_t b) { bytes += arena_round(b); };
-    add(24 * (size_t)n);                                       // label keys in, out, index in;
-                                                               // then the interleaved records
+    add(24 * (size_t)n);                                       // interleaved records
     add(4 * (size_t)n);                                        // index out
     for (int k = 0; k < 8; k++) add(4 * ((size_t)n + 1));     // flag rex rstart keep klen gid goff deepest
     for (int k = 0; k < 7; k++) add(4 * (size_t)n);           // A
@@ -371,13 +362,7 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
     add(4 * model_floats);
     Arena* ar;
     RS_TRY(arena_reserve(AR_BASE, bytes, &ar));
-    // the label sort's keys and input indices share one region, which holds
-    // the interleaved coordinates once they are consumed
-    char* lreg = take<char>(ar, 24 * (size_t)n);
-    uint64_t* lkin = reinterpret_cast<uint64_t*>(lreg);
-    uint64_t* lkout = reinterpret_cast<uint64_t*>(lreg + 8 * (size_t)n);
-    int32_t* lvin = reinterpret_cast<int32_t*>(lreg + 16 * (size_t)n);
-    float2* prec = reinterpret_cast<float2*>(lreg);
+    float2* prec = take<float2>(ar, 3 * (size_t)n);
     int32_t* sidx = take<int32_t>(ar, n);
     int32_t* flag = take<int32_t>(ar, n + 1);
     int32_t* rex = take<int32_t>(ar, n + 1);
@@ -391,6 +376,10 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
     A.x = take<float>(ar, n); A.y = take<float>(ar, n); A.z = take<float>(ar, n);
     A.vx = take<float>(ar, n); A.vy = take<float>(ar, n); A.vz = take<float>(ar, n);
     A.idx = take<int32_t>(ar, n);
+    // the label sort's keys and input indices lie where the members go later
+    uint32_t* lkin = reinterpret_cast<uint32_t*>(A.x);
+    uint32_t* lkout = reinterpret_cast<uint32_t*>(A.y);
+    int32_t* lvin = reinterpret_cast<int32_t*>(A.z);
     NodeRec nr;
     nr.level = take<int32_t>(ar, cap);
     nr.minidx = take<int32_t>(ar, cap);
@@ -426,13 +415,12 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
 
     unsigned gb = grid_for(n, BT, 1ll << 31);
     RS_HIP(hipMemsetAsync(ctr, 0, 32 * sizeof(int32_t), st));
-    k_p_keys<<<gb, BT, 0, st>>>(x, y, z, vx, vy, vz, lab, n, L, lkin, lvin, ctr);
+    k_p_keys<<<gb, BT, 0, st>>>(x, y, z, vx, vy, vz, lab, n, L, lkin, lvin, prec, ctr);
     RS_HIP(hipGetLastError());
     int lbits = 1;
     while (lbits < 31 && ((int64_t)1 << lbits) < n) lbits++;
-    RS_TRY(sort_pairs_u64_i32(lkin, lkout, lvin, sidx, n, lbits, stemp, stb, st));
+    RS_TRY(sort_pairs_u32_i32(lkin, lkout, lvin, sidx, n, lbits, stemp, stb, st));
     k_p_runflag<<<gb, BT, 0, st>>>(n, lkout, flag);
-    k_p_interleave<<<gb, BT, 0, st>>>(n, x, y, z, vx, vy, vz, prec);
     RS_HIP(hipGetLastError());
     RS_TRY(scan_exclusive_i32(flag, rex, n, ctemp, ctr + 1, st));
     k_p_runstart<<<gb, BT, 0, st>>>(n, flag, rex, rstart);
@@ -467,7 +455,8 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
     auto span_pass = [&](hipStream_t s) {
         if (G <= 0) return;
         k_p_span_init<<<grid_for(6 * (int64_t)G, BT, 1ll << 31), BT, 0, s>>>(G, gspan);
-        k_p_span<<<grid_for((n + SPAN_ROWS - 1) / SPAN_ROWS, BT, 1ll << 31), BT, 0, s>>>(n, flag, rex, rstart, keep, gid, goff, A, pp.LQ, gspan);
+        k_p_span<<<grid_for((n + SPAN_ROWS - 1) / SPAN_ROWS, BT, 1ll << 31), BT, 0, s>>>(
+            n, flag, rex, rstart, keep, gid, goff, A, pp.LQ, gspan);
         k_p_wide<<<grid_for(G, BT, 1ll << 31), BT, 0, s>>>(G, gspan, pp.LQ, wide0);
     };
     RS_TRY(fill_i32(nr.count, G, 1, st));

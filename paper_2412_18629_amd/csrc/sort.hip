@@ -1,5 +1,5 @@
-// sort.hip -- stable LSD radix sort of (u64 key, i32 value) pairs over the
-// low `bits` bits of the key, 8-bit digits, one pass per digit (the last
+// sort.hip -- stable LSD radix sort of (u64 or u32 key, i32 value) pairs over
+// the low `bits` bits of the key, 8-bit digits, one pass per digit (the last
 // pass narrower when `bits` is not a multiple of 8).
 //
 // Up to SB_MAX pairs one workgroup runs all passes in LDS (one launch).
@@ -16,12 +16,15 @@
 // Passes alternate between the output and a scratch buffer so the last one
 // lands in the output; the input is never written.
 //
-// What bounds it: memory traffic, 32 bytes a pair and pass (keys twice).  The
+// What bounds it: memory traffic, 32 bytes a pair and pass of 64-bit keys, 20
+// of 32-bit ones (keys read twice).  The
 // scatter reaches the rate of a plain copy only when the lines that
 // neighbouring tiles share are completed in one L2 (see the tile order
 // below): 134M pairs, five passes, 9.03 -> 4.86 ms, its scatter 1.33 -> 0.70
 // ms a pass (4.6 TB/s); with the tiles in launch order 8.3 ms.  12M pairs of
 // 64-bit keys: 1.36 -> 0.77 ms.
+#include <algorithm>
+
 #include "common.h"
 
 namespace rs {
@@ -75,9 +78,9 @@ RS_DEV int32_t digit_scan(int32_t v, int32_t* part /* [4] */) {
 // Tiles are dealt so that consecutive ones run on one XCD: their runs of one
 // digit are neighbours in the output, and the lines they share are completed
 // in one L2 instead of being written back in parts by several.
-template <int RB_I>
+template <typename K, int RB_I>
 __global__ void __launch_bounds__(RB_T)
-k_rsort_hist(const uint64_t* __restrict__ keys, int64_t n, int shift, uint32_t dmask, int ntiles,
+k_rsort_hist(const K* __restrict__ keys, int64_t n, int shift, uint32_t dmask, int ntiles,
              int chunk, int32_t* __restrict__ cnt) {
     constexpr int RB_TILE = RB_T * RB_I;
     __shared__ int32_t h[RB_W][RB_D];
@@ -143,14 +146,14 @@ k_rsort_scan(int ntiles, int32_t* __restrict__ cnt, int32_t* __restrict__ total)
     if (tid == 0) total[blockIdx.x] = carry;
 }
 
-template <int RB_I>
+template <typename K, int RB_I>
 __global__ void __launch_bounds__(RB_T)
-k_rsort_scatter(const uint64_t* __restrict__ kin, const int32_t* __restrict__ vin,
-                uint64_t* __restrict__ kout, int32_t* __restrict__ vout, int64_t n, int shift,
+k_rsort_scatter(const K* __restrict__ kin, const int32_t* __restrict__ vin,
+                K* __restrict__ kout, int32_t* __restrict__ vout, int64_t n, int shift,
                 uint32_t dmask, int ntiles, int chunk, const int32_t* __restrict__ offs,
                 const int32_t* __restrict__ total) {
     constexpr int RB_TILE = RB_T * RB_I;
-    __shared__ uint64_t sk[RB_TILE];   // keys in digit order, then the values
+    __shared__ K sk[RB_TILE];          // keys in digit order, then the values
     __shared__ int32_t wc[RB_W][RB_D]; // per wavefront: keys of each digit (then offsets)
     __shared__ int32_t gbase[RB_D];    // global slot of a digit's first key, less its tile slot
     __shared__ int32_t part[4];
@@ -163,7 +166,7 @@ k_rsort_scatter(const uint64_t* __restrict__ kin, const int32_t* __restrict__ vi
 
     // each wavefront ranks its own contiguous run of RB_I * 64 keys in input
     // order: digit peers by ballots, running per-digit counts in its own LDS row
-    uint64_t k[RB_I];
+    K k[RB_I];
     int32_t v[RB_I];
     int rk[RB_I];
     const int64_t wbase = base + (int64_t)w * RB_I * 64;
@@ -211,7 +214,7 @@ k_rsort_scatter(const uint64_t* __restrict__ kin, const int32_t* __restrict__ vi
     for (int r = 0; r < RB_I; r++) {
         const int j = r * RB_T + tid;
         if (j < nt) {
-            const uint64_t kk = sk[j];
+            const K kk = sk[j];
             g[r] = gbase[(int)((kk >> shift) & dmask)] + j;
             kout[g[r]] = kk;
         }
@@ -233,18 +236,19 @@ k_rsort_scatter(const uint64_t* __restrict__ kin, const int32_t* __restrict__ vi
 // bits 47 us in nine launches, 20 us in one.
 constexpr int SB_T = 1024, SB_W = SB_T / 64, SB_I = 8, SB_MAX = SB_T * SB_I;
 
+template <typename K>
 __global__ void __launch_bounds__(SB_T)
-k_rsort_block(const uint64_t* __restrict__ kin, const int32_t* __restrict__ vin,
-              uint64_t* __restrict__ kout, int32_t* __restrict__ vout, int n, int bits) {
+k_rsort_block(const K* __restrict__ kin, const int32_t* __restrict__ vin, K* __restrict__ kout,
+              int32_t* __restrict__ vout, int n, int bits) {
     extern __shared__ __align__(16) char smem[];
-    uint64_t* sk = reinterpret_cast<uint64_t*>(smem);              // [SB_MAX]
+    K* sk = reinterpret_cast<K*>(smem);                            // [SB_MAX]
     int32_t* sv = reinterpret_cast<int32_t*>(sk + SB_MAX);         // [SB_MAX]
     int32_t* wc = sv + SB_MAX;                                     // [SB_W][RB_D]
     __shared__ int32_t part[4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int rounds = (n + SB_T - 1) / SB_T;                      // keys per thread in use
     const int wbase = w * rounds * 64;
-    uint64_t k[SB_I];
+    K k[SB_I];
     int32_t v[SB_I];
     int rk[SB_I];
 #pragma unroll
@@ -306,21 +310,21 @@ k_rsort_block(const uint64_t* __restrict__ kin, const int32_t* __restrict__ vin,
 // Work space: a scratch pair of arrays, and at least the digit counts and
 // totals.  Sized for 2048-key tiles and a second table as well, which the
 // callers' limits (the work space of fixed size) are documented for.
-size_t sort_temp_bytes(int64_t n) {
+size_t sort_temp_bytes(int64_t n, size_t key_bytes) {
     if (n < 1) n = 1;
     const int64_t nc = RB_D * ((n + 2047) / 2048);
-    return arena_round((size_t)n * 8) + arena_round((size_t)n * 4) +
+    return arena_round((size_t)n * key_bytes) + arena_round((size_t)n * 4) +
            2 * arena_round((size_t)nc * 4) + arena_round(scan_temp_bytes(nc));
 }
 
-template <int I>
-static int sort_passes(const uint64_t* kin, uint64_t* kout, const int32_t* vin, int32_t* vout,
-                       int64_t n, int bits, void* temp, hipStream_t st) {
+template <typename K, int I>
+static int sort_passes(const K* kin, K* kout, const int32_t* vin, int32_t* vout, int64_t n,
+                       int bits, void* temp, hipStream_t st) {
     const int passes = (bits + 7) / 8;
     const int64_t ntiles = (n + RB_T * I - 1) / (RB_T * I);
     char* p = static_cast<char*>(temp);
-    uint64_t* kalt = reinterpret_cast<uint64_t*>(p);
-    p += arena_round((size_t)n * 8);
+    K* kalt = reinterpret_cast<K*>(p);
+    p += arena_round((size_t)n * sizeof(K));
     int32_t* valt = reinterpret_cast<int32_t*>(p);
     p += arena_round((size_t)n * 4);
     int32_t* cnt = reinterpret_cast<int32_t*>(p);
@@ -331,19 +335,19 @@ static int sort_passes(const uint64_t* kin, uint64_t* kout, const int32_t* vin, 
     const int64_t per = ntiles / (16 * XCDS);
     const int chunk = per < 1 ? 1 : per > RB_CHUNK ? RB_CHUNK : (int)per;
     const unsigned grid = (unsigned)xcd_chunk_grid((int)ntiles, chunk);
-    const uint64_t* sk = kin;
+    const K* sk = kin;
     const int32_t* svv = vin;
     for (int pass = 0; pass < passes; pass++) {
         const bool to_out = ((passes - 1 - pass) % 2) == 0;
-        uint64_t* dk = to_out ? kout : kalt;
+        K* dk = to_out ? kout : kalt;
         int32_t* dv = to_out ? vout : valt;
         const int shift = 8 * pass;
         const int db = bits - shift < 8 ? bits - shift : 8;   // digit width of this pass
         const uint32_t dmask = (1u << db) - 1u;
-        k_rsort_hist<I><<<grid, RB_T, 0, st>>>(sk, n, shift, dmask, (int)ntiles, chunk, cnt);
+        k_rsort_hist<K, I><<<grid, RB_T, 0, st>>>(sk, n, shift, dmask, (int)ntiles, chunk, cnt);
         k_rsort_scan<<<RB_D, RS_T, 0, st>>>((int)ntiles, cnt, total);
-        k_rsort_scatter<I><<<grid, RB_T, 0, st>>>(sk, svv, dk, dv, n, shift, dmask, (int)ntiles,
-                                                  chunk, cnt, total);
+        k_rsort_scatter<K, I><<<grid, RB_T, 0, st>>>(sk, svv, dk, dv, n, shift, dmask,
+                                                     (int)ntiles, chunk, cnt, total);
         RS_HIP(hipGetLastError());
         sk = dk;
         svv = dv;
@@ -351,24 +355,35 @@ static int sort_passes(const uint64_t* kin, uint64_t* kout, const int32_t* vin, 
     return RS_OK;
 }
 
-int sort_pairs_u64_i32(const uint64_t* kin, uint64_t* kout, const int32_t* vin,
-                       int32_t* vout, int64_t n, int bits, void* temp, size_t temp_bytes,
-                       hipStream_t st) {
+template <typename K>
+static int sort_pairs(const K* kin, K* kout, const int32_t* vin, int32_t* vout, int64_t n,
+                      int bits, void* temp, size_t temp_bytes, hipStream_t st) {
     if (n <= 0) return RS_OK;
     if (n >= ((int64_t)1 << 31)) return RS_EINVAL;
-    if (temp_bytes < sort_temp_bytes(n) || !temp) return RS_EINTERNAL;
-    if (bits < 1) bits = 1;
-    if (bits > 64) bits = 64;
+    if (temp_bytes < sort_temp_bytes(n, sizeof(K)) || !temp) return RS_EINTERNAL;
+    bits = std::max(1, std::min(bits, (int)(8 * sizeof(K))));
     if (n <= SB_MAX) {
-        const size_t lds = (size_t)SB_MAX * 12 + (size_t)SB_W * RB_D * 4;
-        RS_HIP(hipFuncSetAttribute((const void*)k_rsort_block,
+        const size_t lds = (size_t)SB_MAX * (sizeof(K) + 4) + (size_t)SB_W * RB_D * 4;
+        RS_HIP(hipFuncSetAttribute((const void*)k_rsort_block<K>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        k_rsort_block<<<1, SB_T, lds, st>>>(kin, vin, kout, vout, (int)n, bits);
+        k_rsort_block<K><<<1, SB_T, lds, st>>>(kin, vin, kout, vout, (int)n, bits);
         RS_HIP(hipGetLastError());
         return RS_OK;
     }
-    return n < RB_LONG ? sort_passes<8>(kin, kout, vin, vout, n, bits, temp, st)
-                       : sort_passes<16>(kin, kout, vin, vout, n, bits, temp, st);
+    return n < RB_LONG ? sort_passes<K, 8>(kin, kout, vin, vout, n, bits, temp, st)
+                       : sort_passes<K, 16>(kin, kout, vin, vout, n, bits, temp, st);
+}
+
+int sort_pairs_u64_i32(const uint64_t* kin, uint64_t* kout, const int32_t* vin,
+                       int32_t* vout, int64_t n, int bits, void* temp, size_t temp_bytes,
+                       hipStream_t st) {
+    return sort_pairs(kin, kout, vin, vout, n, bits, temp, temp_bytes, st);
+}
+
+int sort_pairs_u32_i32(const uint32_t* kin, uint32_t* kout, const int32_t* vin,
+                       int32_t* vout, int64_t n, int bits, void* temp, size_t temp_bytes,
+                       hipStream_t st) {
+    return sort_pairs(kin, kout, vin, vout, n, bits, temp, temp_bytes, st);
 }
 
 }  // namespace rs
