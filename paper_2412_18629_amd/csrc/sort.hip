@@ -93,7 +93,19 @@ k_rsort_hist(const K* __restrict__ keys, int64_t n, int shift, uint32_t dmask, i
 #pragma unroll
     for (int r = 0; r < RB_I; r++) {
         const int64_t i = base + r * RB_T + tid;
-        if (i < n) atomicAdd(&h[w][(int)((keys[i] >> shift) & dmask)], 1);
+        if (i >= n) continue;
+        const int d = (int)((keys[i] >> shift) & dmask);
+        if constexpr (sizeof(K) == 4) {
+            // 32-bit keys are labels and node indices, many of them equal: the lanes
+            // with the first lane's digit count as one addition (16.7M members by
+            // node, three passes 127 -> 77 us; 64-bit keys 0.18 -> 0.19 ms)
+            const int d0 = __builtin_amdgcn_readfirstlane(d);
+            const uint64_t same = __ballot(d == d0);
+            if (d != d0) atomicAdd(&h[w][d], 1);
+            else if ((same & lanemask_lt()) == 0) atomicAdd(&h[w][d], __popcll(same));
+        } else {
+            atomicAdd(&h[w][d], 1);
+        }
     }
     __syncthreads();
     if (tid < RB_D) {
