@@ -122,7 +122,8 @@ __global__ void k_p_deepest(int64_t n, const int32_t* __restrict__ lab,
 // displacement of its members from the reference member (the first packed
 // member, the smallest index), in the nearest periodic image exactly as for
 // the dispersions.  Stored offset by 2^62 so that unsigned atomics order
-// them.  A wavefront goes through SPAN_ROWS rows of 64 members and reduces a
+// them.  A wavefront goes through up to SPAN_ROWS rows of 64 members (fewer
+// where that would leave less than 4096 wavefronts) and reduces a
 // group's extremes once, where the group ends or its rows do (members are
 // packed per group): with a reduction and six atomics a row, the atomics on
 // large groups' extremes set the time (134M members 10.5 -> 1.6 ms beside the
@@ -139,7 +140,7 @@ __global__ void k_p_span(int64_t n, const int32_t* __restrict__ flag,
                          const int32_t* __restrict__ rex, const int32_t* __restrict__ rstart,
                          const int32_t* __restrict__ keep, const int32_t* __restrict__ gid,
                          const int32_t* __restrict__ goff, Members A, int64_t LQ,
-                         unsigned long long* __restrict__ span) {
+                         int rows, unsigned long long* __restrict__ span) {
     const int lane = threadIdx.x & 63;
     const int64_t w = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6);
     const float* ax3[3] = {A.x, A.y, A.z};
@@ -158,8 +159,8 @@ __global__ void k_p_span(int64_t n, const int32_t* __restrict__ flag,
             }
         }
     };
-    for (int row = 0; row < SPAN_ROWS; row++) {
-        const int64_t p = (w * SPAN_ROWS + row) * 64 + lane;
+    for (int row = 0; row < rows; row++) {
+        const int64_t p = (w * rows + row) * 64 + lane;
         bool ok = p < n;
         const int32_t r = ok ? rex[p] + flag[p] - 1 : 0;
         ok = ok && keep[r];
@@ -316,13 +317,14 @@ void tree_release(rs_tree* t) {
 
 // Side streams (default priority) and ordering events per device, created on
 // first use and kept for the process.  Stream 0 takes the level-0 small
-// subtrees, stream 1 the small children of each large-node level.
+// subtrees, stream 1 the small children of each large-node level, stream 2
+// the smaller ones of both.
 static int side_stream(int which, hipStream_t* s, hipEvent_t* ready, hipEvent_t* done) {
-    static hipStream_t g_s[64][2];
-    static hipEvent_t g_r[64][2], g_d[64][2];
+    static hipStream_t g_s[64][3];
+    static hipEvent_t g_r[64][3], g_d[64][3];
     int dev = 0;
     RS_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 64 || which < 0 || which > 1) return RS_EDEVICE;
+    if (dev < 0 || dev >= 64 || which < 0 || which > 2) return RS_EDEVICE;
     if (!g_s[dev][which]) {
         RS_HIP(hipStreamCreateWithFlags(&g_s[dev][which], hipStreamNonBlocking));
         RS_HIP(hipEventCreateWithFlags(&g_r[dev][which], hipEventDisableTiming));
@@ -455,8 +457,9 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
     auto span_pass = [&](hipStream_t s) {
         if (G <= 0) return;
         k_p_span_init<<<grid_for(6 * (int64_t)G, BT, 1ll << 31), BT, 0, s>>>(G, gspan);
-        k_p_span<<<grid_for((n + SPAN_ROWS - 1) / SPAN_ROWS, BT, 1ll << 31), BT, 0, s>>>(
-            n, flag, rex, rstart, keep, gid, goff, A, pp.LQ, gspan);
+        const int rows = (int)std::max<int64_t>(1, std::min<int64_t>(SPAN_ROWS, n >> 18));
+        k_p_span<<<grid_for((n + rows - 1) / rows, BT, 1ll << 31), BT, 0, s>>>(
+            n, flag, rex, rstart, keep, gid, goff, A, pp.LQ, rows, gspan);
         k_p_wide<<<grid_for(G, BT, 1ll << 31), BT, 0, s>>>(G, gspan, pp.LQ, wide0);
     };
     RS_TRY(fill_i32(nr.count, G, 1, st));
@@ -561,13 +564,12 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
         hipEvent_t ready = nullptr, done = nullptr;
         RS_TRY(side_stream(0, &s2, &ready, &done));
         RS_TRY(side_stream(1, &lw.side, &lw.side_ready, &lw.side_done));
+        RS_TRY(side_stream(2, &lw.fork.stream, &lw.fork.ready, &lw.fork.done));
         lw.side_pending = false;
         RS_HIP(hipEventRecord(ready, st));
         RS_HIP(hipStreamWaitEvent(s2, ready, 0));
-        int rc = RS_OK;
-        for (int b = 3; b >= 0 && rc == RS_OK; b--)
-            rc = run_small_bucket(b, buckets + b * bstride, bcnt[b], A, nr, pp, deepest, s2,
-                                  "phase_small_level0");
+        int rc = run_small_buckets(buckets, bstride, bcnt, A, nr, pp, deepest, s2, lw.fork,
+                                   "phase_small_level0");
         span_pass(s2);
         if (rc == RS_OK && hipGetLastError() != hipSuccess) rc = RS_EDEVICE;
         size_t li = 0;
@@ -593,11 +595,13 @@ static int phase_attempt(const float* x, const float* y, const float* z, const f
             (void)hipGetLastError();
             (void)hipStreamSynchronize(s2);
             (void)hipStreamSynchronize(lw.side);
+            (void)hipStreamSynchronize(lw.fork.stream);
             return rc != RS_OK ? rc : RS_EDEVICE;
         }
         if (rc != RS_OK) {
             (void)hipStreamSynchronize(s2);
             (void)hipStreamSynchronize(lw.side);
+            (void)hipStreamSynchronize(lw.fork.stream);
             return rc;
         }
     }

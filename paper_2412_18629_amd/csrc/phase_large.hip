@@ -803,9 +803,8 @@ int launch_small_items(LargeWork* w, const SmallItem* items, int n, const Member
         RS_HIP(hipStreamWaitEvent(w->side, w->side_ready, 0));
         ls = w->side;
     }
-    for (int b = 3; b >= 0; b--)
-        RS_TRY(run_small_bucket(b, w->buckets + b * w->cap_small, cnts[b], mb, nr, pp, deepest, ls,
-                                w->side ? "phase_small_children" : "phase_small"));
+    RS_TRY(run_small_buckets(w->buckets, w->cap_small, cnts, mb, nr, pp, deepest, ls, w->fork,
+                             w->side ? "phase_small_children" : "phase_small"));
     if (w->side) {
         RS_HIP(hipEventRecord(w->side_done, w->side));
         w->side_pending = true;

@@ -885,4 +885,27 @@ int run_small_bucket(int b, const SmallItem* items, int n_items, const Members& 
     }
 }
 
+int run_small_buckets(const SmallItem* buckets, int64_t stride, const int32_t* counts,
+                      const Members& mb, const NodeRec& nr, const PhaseParams& pp,
+                      int32_t* deepest, hipStream_t st, const SmallFork& fork,
+                      const char* timer) {
+    const bool split =
+        fork.stream && counts[3] > 0 && (counts[0] > 0 || counts[1] > 0 || counts[2] > 0);
+    hipStream_t low = split ? fork.stream : st;
+    if (split) {
+        RS_HIP(hipEventRecord(fork.ready, st));
+        RS_HIP(hipStreamWaitEvent(low, fork.ready, 0));
+    }
+    int rc = RS_OK;
+    for (int b = 3; b >= 0 && rc == RS_OK; b--)
+        rc = run_small_bucket(b, buckets + b * stride, counts[b], mb, nr, pp, deepest,
+                              b == 3 ? st : low, timer);
+    if (split) {
+        // also after a failure: what has been launched ends before `st` goes on
+        RS_HIP(hipEventRecord(fork.done, low));
+        RS_HIP(hipStreamWaitEvent(st, fork.done, 0));
+    }
+    return rc;
+}
+
 }  // namespace rs
