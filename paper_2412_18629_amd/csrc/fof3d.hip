@@ -18,7 +18,7 @@
 //              being linked already); octant pairs in the 27-cell
 //              neighbourhood are tested with early exit on the first linked
 //              pair and skipped when already in one component.  Pairs of
-//              more than heavy_pairs member pairs are queued and tested
+//              more than HEAVY_PAIRS member pairs are queued and tested
 //              afterwards, one wavefront per pair.  Without auto-link (grids
 //              of under three cells per axis, or octants too wide) the
 //              union-find runs over slots and every member pair is tested.
@@ -287,21 +287,17 @@ struct LinkArgs {
     int2* heavy;                // deferred octant pairs (auto-link) ...
     int32_t* n_heavy;           // ... their count (may exceed the capacity)
     int32_t cap_heavy;
-    int64_t heavy_pairs;        // deferred above this many member pairs
 };
 
-// Octant pairs with more than heavy_pairs member pairs are deferred to a
+// Octant pairs with more than HEAVY_PAIRS member pairs are deferred to a
 // second pass, run one wavefront per pair once every lighter pair has been
 // linked: by then most of them already share a root, and the rest are
-// searched 64 member pairs at a time instead of serially by one thread.
-// While the octants do not fill the chip many times over, the pass ends with
-// its slowest thread, and a low limit shortens that (1M clustered particles
-// 1.63 -> 0.99 ms, 2.1M 1.85 -> 1.53 ms with 128 for 1024); beyond, the
-// slow threads are hidden and deferring costs more than it saves (30M
-// particles 13.05 ms with 1024, 13.2 with 256, 13.9 with 128).  With 32 the
-// queue overflows.
-constexpr int64_t HEAVY_FEW = 128, HEAVY_MANY = 1024;
-constexpr int32_t HEAVY_FEW_OCT = 1 << 22;   // octants up to which HEAVY_FEW holds
+// searched 64 member pairs at a time instead of serially by one thread.  A
+// lower limit defers the pairs that would have joined the others' components:
+// the queue fills, the largest pairs no longer find room, and single threads
+// test them (6M clustered particles, link length one mean spacing: 4.5 ms,
+// with a limit of 128 213 ms).
+constexpr int64_t HEAVY_PAIRS = 1024;
 
 // cells of row rr (cell indices [b, e))
 RS_DEV void row_cells(const LinkArgs& A, uint64_t rr, int32_t& b, int32_t& e) {
@@ -424,7 +420,7 @@ RS_DEV void link_cell(const LinkArgs& A, int32_t a, int32_t s0, int32_t s1, int 
                 __hip_atomic_store(A.parent + b, rb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (ra == rb) continue;
             const int32_t t0 = A.oct_start[b], t1 = A.oct_start[b + 1];
-            if ((int64_t)(s1 - s0) * (t1 - t0) > A.heavy_pairs) {
+            if ((int64_t)(s1 - s0) * (t1 - t0) > HEAVY_PAIRS) {
                 const int32_t q = atomicAdd(A.n_heavy, 1);
                 if (q < A.cap_heavy) {
                     A.heavy[q] = make_int2(a, b);
@@ -455,11 +451,11 @@ RS_DEV void link_cell(const LinkArgs& A, int32_t a, int32_t s0, int32_t s1, int 
 // blockIdx.y.  A thread's walk is a serial chain of dependent loads, 236 us
 // long even for a few thousand octants; a thread that walks all cells meets
 // most octants with its own root already known, which pays once the octants
-// fill the chip: split up to SPLIT_OCT octants (5000 particles 314 -> 179 us
-// a call, 250k clustered 1.36 -> 1.09 ms, 250k unclustered 222 -> 212 us), and
-// up to SPLIT_DENSE where octants hold 1.5 particles or more, so that the
-// walks are long (1M clustered 0.99 -> 0.77 ms, 2.1M 1.53 -> 1.42 ms; but 1M
-// unclustered 0.35 -> 0.43 ms).  Octants are numbered in cell-key order, so cells
+// fill the chip: split up to SPLIT_OCT octants (5000 particles 241 -> 188 us
+// a call, 250k unclustered 229 -> 214 us, 250k clustered 629 -> 621), and up
+// to SPLIT_DENSE where octants hold 1.5 particles or more, so that the walks
+// are long (1M clustered 1.53 -> 0.90 ms, 2.1M 1.88 -> 1.37 ms; but 1M
+// unclustered 0.33 -> 0.41 ms).  Octants are numbered in cell-key order, so cells
 // with a smaller key (among them every cell of an earlier row) hold only
 // earlier octants, whose pairs with this one are taken from their side.
 constexpr int32_t SPLIT_OCT = 1 << 18, SPLIT_DENSE = 1 << 21;
@@ -539,8 +535,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
 
 // the deferred octant pairs, one wavefront per pair (grid-stride): skipped
 // when already in one component, otherwise the member pairs are tested 64
-// at a time until the first one within ll
+// at a time until the first one within ll, or until they are
 constexpr int HEAVY_BLOCKS = 8192;
+// A wavefront inside a large pair looks again, every so many of its 64-pair
+// steps, whether others have joined the two components meanwhile (500k
+// clustered particles, link length 1.3 mean spacings: 7.6 -> 1.1 ms; with 256
+// and 1024 steps the same within 3 %, without it up to 7 ms depending on which
+// pairs happen to run first).
+constexpr int HEAVY_RECHECK = 64;
 
 template <bool PER, bool CNT>
 __global__ void __launch_bounds__(64) k_link_heavy(LinkArgs A) {
@@ -555,9 +557,16 @@ __global__ void __launch_bounds__(64) k_link_heavy(LinkArgs A) {
         const int32_t s0 = A.oct_start[pr.x], s1 = A.oct_start[pr.x + 1];
         const int32_t t0 = A.oct_start[pr.y], t1 = A.oct_start[pr.y + 1];
         bool hit = false;
+        int steps = 0;
         for (int32_t i = s0; i < s1 && !hit; i++) {
+            if (steps >= HEAVY_RECHECK) {
+                if (__builtin_amdgcn_readfirstlane(uf_root(A.parent, ra)) ==
+                    __builtin_amdgcn_readfirstlane(uf_root(A.parent, rb)))
+                    break;
+                steps = 0;
+            }
             const float xi = A.sx[i], yi = A.sy[i], zi = A.sz[i];
-            for (int32_t j0 = t0; j0 < t1 && !hit; j0 += 64) {
+            for (int32_t j0 = t0; j0 < t1 && !hit; j0 += 64, steps++) {
                 const int32_t j = j0 + lane;
                 const bool near = j < t1 && link_d2<PER>(xi, yi, zi, A.sx[j], A.sy[j],
                                                          A.sz[j], g) <= g.ll2;
@@ -834,8 +843,7 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
         if (v >= 0 && v < qcap) qcap = v;
     }
     LinkArgs A{oct_start, oct_bits, cell_oct, cell_key, row_start, cnt + 1, kout, sx, sy, sz,
-               g.autolink ? poct : parent, minidx, g, heavy, cnt + 3, (int32_t)qcap,
-               max_oct <= HEAVY_FEW_OCT ? HEAVY_FEW : HEAVY_MANY};
+               g.autolink ? poct : parent, minidx, g, heavy, cnt + 3, (int32_t)qcap};
     if (instrument) prof_begin("fof3d_link", st);
     RS_TRY(B.periodic ? link_pass<true>(A, n, max_oct, st)
                        : link_pass<false>(A, n, max_oct, st));
