@@ -279,6 +279,7 @@ struct LinkArgs {
     const uint64_t* cell_key;   // [n_cell], ascending
     const int32_t* row_start;   // [nc^2 + 1], or null: rows found by binary search
     const int32_t* counts;      // [0] octants, [1] cells
+    const int32_t* err;         // set: a coordinate is out of range, nothing to link
     const uint64_t* keys;       // sorted keys
     const float *sx, *sy, *sz;  // sorted positions
     int32_t* parent;            // union-find over octants (auto-link) or over slots
@@ -463,7 +464,7 @@ constexpr int32_t SPLIT_OCT = 1 << 18, SPLIT_DENSE = 1 << 21;
 template <bool AUTOLINK, bool PER, bool CNT, bool SPLIT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k_link(LinkArgs A) {
     const int32_t a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= A.counts[0]) return;
+    if (a >= A.counts[0] || *A.err) return;
     unsigned long long npairs = 0;   // counting build only
     const Grid3& g = A.g;
     const int32_t s0 = A.oct_start[a], s1 = A.oct_start[a + 1];
@@ -548,7 +549,7 @@ template <bool PER, bool CNT>
 __global__ void __launch_bounds__(64) k_link_heavy(LinkArgs A) {
     const int lane = threadIdx.x;
     unsigned long long npairs = 0;   // counting build only
-    const int32_t nq = min(*A.n_heavy, A.cap_heavy);
+    const int32_t nq = min(*A.n_heavy, A.cap_heavy);   // none when *A.err is set
     const Grid3& g = A.g;
     for (int32_t q = blockIdx.x; q < nq; q += gridDim.x) {
         const int2 pr = A.heavy[q];
@@ -767,7 +768,9 @@ static int link_pass(const LinkArgs& A, int64_t n, int32_t max_oct, hipStream_t 
 // Up to this many particles the launches after the tables cover as many
 // octants as particles and read the counts on the device, which saves the
 // host's wait for them (some 25 us of a 400 us call); above, the idle threads
-// would cost more.
+// would cost more.  A range error is then read with the group count, after
+// the launches: the link finds it on the device and tests nothing (the
+// particles out of range all lie in the first cell, whose pairs are many).
 constexpr int64_t FEW_PARTICLES = 1 << 16;
 
 // One 3D pass over the work space `ar` (at least fof3d_bytes(n, g), its bump
@@ -842,7 +845,7 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
         const int64_t v = atoll(e);
         if (v >= 0 && v < qcap) qcap = v;
     }
-    LinkArgs A{oct_start, oct_bits, cell_oct, cell_key, row_start, cnt + 1, kout, sx, sy, sz,
+    LinkArgs A{oct_start, oct_bits, cell_oct, cell_key, row_start, cnt + 1, cnt, kout, sx, sy, sz,
                g.autolink ? poct : parent, minidx, g, heavy, cnt + 3, (int32_t)qcap};
     if (instrument) prof_begin("fof3d_link", st);
     RS_TRY(B.periodic ? link_pass<true>(A, n, max_oct, st)
