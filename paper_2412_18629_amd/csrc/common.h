@@ -171,9 +171,15 @@ RS_DEV uint32_t wave_min_u32(uint32_t v) {
 // so at most 8 in the sum), of the norms (8), of the products and their
 // summation (at most 24) and of the exact d^2 itself (8 units of d^2, which
 // is at most 2 (|Xi|^2 + |Xj|^2)).
+//
+// In the denormal range roundings are no longer relative: a squared norm or
+// coordinate sum may be off by a few units of 2^-149 (2^-126 each, should the
+// products flush), and d^2 = a Dx + c Dv by that times a and c.  lb_abs() is
+// above all of it together, and far below any d^2 of the normal range.
 // ---------------------------------------------------------------------------
 
 constexpr float LB_EPS = 3.814697265625e-06f;
+RS_DEV float lb_abs(float a, float c) { return 1e-36f * (1.0f + a + c); }
 constexpr float NORM_PAD = 1e30f;   // value of absent rows and columns
 // Across a periodic face X also carries the absolute rounding of the image
 // shift, at most eta = sqrt(a) box_slack(L) per pair of positions, and

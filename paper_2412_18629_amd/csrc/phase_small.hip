@@ -487,6 +487,7 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
             // the node spans less than half the box; a wider one (it
             // percolates) has every pair evaluated.
             bool wide = false;
+            const float tiny = lb_abs(fa, fc);
             float lb_k = 0.0f, lb_add = 0.0f;
             if (!nowrap) {
 #pragma unroll
@@ -578,7 +579,8 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
                     row = row < sz ? row : 0;
                     const Member pr = load_member(mb, it.off + perm[s0 + row]);
                     const float d = member_d2(pq, pr, nowrap, fa, fc, pp);
-                    const bool ok = q < sz && row != q && d <= (bound - lb_add) * (1.0f - lb_k);
+                    const bool ok = q < sz && row != q &&
+                                    d <= (bound - lb_add) * (1.0f - lb_k) - tiny;
                     if (ok) d2[q] = d;
                     again &= ~__ballot(ok);
                 }
@@ -655,7 +657,8 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
             {
                 const int nc = sh[SH_NC], ngl = (nc + 63) >> 6;
                 const float thr = wide ? NORM_WIDE
-                                       : (l2 * (1.0f + lb_k) + lb_add) * (nowrap ? 1.0f : 1.00001f);
+                                       : (l2 * (1.0f + lb_k) + lb_add) *
+                                                 (nowrap ? 1.0f : 1.00001f) + tiny;
                 int qn = 0;   // queued pairs (uniform)
                 auto drain = [&](int count) {
                     __builtin_amdgcn_wave_barrier();

@@ -235,7 +235,9 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
     const int lm = lane & 15, lk = lane >> 4, lkb = lk < 2 ? lk : 2;
     // A pair is a candidate when its bound does not exceed the threshold (with
     // the slack of image shifts where the node has them); the tiny constant
-    // makes the difference negative for coinciding points at threshold 0.
+    // makes the difference negative for coinciding points at threshold 0, and
+    // covers the denormal range.
+    const float tiny = 1e-30f + lb_abs(P.a, P.c);
     const float eta = sqrtf(P.a) * box_slack(pp.L);
     auto slacked = [&](float r2) {
         return P.nowrap ? r2
@@ -244,8 +246,8 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
     const float norm = xload<O32>(A.X.b, 3 * mm + 2);
     auto set_threshold = [&](float r2) {
         const float thr = slacked(r2);
-        qX[7 * QS + lane] = norm - (thr * 1.000001f + 1e-30f);
-        qX[8 * QS + lane] = 4.0f * (thr * 1.00001f + 1e-30f);
+        qX[7 * QS + lane] = norm - (thr * 1.000001f + tiny);
+        qX[8 * QS + lane] = 4.0f * (thr * 1.00001f + tiny);
     };
 #pragma unroll
     for (int k = 0; k < 4; k++) qX[k * QS + lane] = -2.0f * xload<O32>(A.X.a, 4 * mm + k);

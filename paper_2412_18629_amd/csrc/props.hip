@@ -605,7 +605,7 @@ __global__ void k_sd_seeds(PrTree T, const int32_t* __restrict__ childsum,
     }
     const float eta = L * 2.3841858e-07f;
     const float k0 = (a * n2 + c * v2) * (1.0f - LB_EPS) -
-                     a * (3.01f * (1.0f + 1.0f / LB_WRAP)) * eta * eta;
+                     a * (3.01f * (1.0f + 1.0f / LB_WRAP)) * eta * eta - lb_abs(a, c);
     if (!(a >= 0.0f) || !(c >= 0.0f) || !(a < 1e18f) || !(c < 1e18f) || !(fabsf(k0) < 1e24f))
         fl |= SD_EXACT;
 #pragma unroll
