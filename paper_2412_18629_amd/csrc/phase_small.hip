@@ -42,10 +42,12 @@ namespace rs {
 enum { SH_SP, SH_NSMALL, SH_NEXT, SH_NC, SH_NCH, SH_BASE, SH_OK, SH_TOT, SH_BUCKET, SH_KK,
        SH_NOWRAP, SH_N };
 
-// a pushed node: members perm[s0, s0 + size), ref = member of smallest index
+// a pushed node: members perm[s0, s0 + size), ref = member of smallest index,
+// depth below the workgroup's item (whose own level has no such bound; every
+// split loses a member, so a depth stays below the item's size)
 struct StackEntry {
     int32_t slot;
-    uint16_t s0, size, ref, level;
+    uint16_t s0, size, ref, depth;
 };
 
 constexpr int WAVE_MAX = 64;      // nodes one wavefront splits by itself
@@ -320,7 +322,7 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
         const SmallItem it = items[w];
         const int n = it.size;
         if (tid == 0) {
-            stk[0] = StackEntry{it.slot, 0, (uint16_t)n, 0, (uint16_t)it.level};
+            stk[0] = StackEntry{it.slot, 0, (uint16_t)n, 0, 0};
             sh[SH_SP] = 1;
             sh[SH_NSMALL] = 0;
         }
@@ -337,7 +339,7 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
             const int sp = sh[SH_SP];
             if (sp == 0) break;
             const StackEntry e = stk[sp - 1];
-            const int s0 = e.s0, sz = e.size, slot = e.slot, level = e.level;
+            const int s0 = e.s0, sz = e.size, slot = e.slot, level = it.level + e.depth;
             __syncthreads();                 // every thread has read the stack
             if (tid == 0) {
                 sh[SH_SP] = sp - 1;
@@ -789,7 +791,7 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
                         nr.size[cs] = size;
                         cnt[ch[5 * c + 0]] = -(c + 1);
                         const StackEntry ce = {cs, (uint16_t)(s0 + ch[5 * c + 4]), (uint16_t)size,
-                                               (uint16_t)ch[5 * c + 3], (uint16_t)(level + 1)};
+                                               (uint16_t)ch[5 * c + 3], (uint16_t)(e.depth + 1)};
                         if (size > WAVE_MAX) stk[atomicAdd(sh + SH_SP, 1)] = ce;
                         else stk[capn - 1 - atomicAdd(sh + SH_NSMALL, 1)] = ce;
                     }
@@ -826,7 +828,8 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
             const int64_t g = it.off + perm[e.s0 + (lane < sz ? lane : 0)];
             wave_subtree<FEAT>(sz >= 64 ? ~0ull : (1ull << sz) - 1, load_member(mb, g), mb.idx[g],
                                __builtin_amdgcn_readfirstlane(e.slot),
-                               __builtin_amdgcn_readfirstlane((int)e.level), pp, nr, deepest);
+                               __builtin_amdgcn_readfirstlane(it.level + (int)e.depth), pp, nr,
+                               deepest);
         }
         __syncthreads();
     }
