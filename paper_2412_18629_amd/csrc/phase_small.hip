@@ -15,7 +15,8 @@
 //      method defines it (see LB_EPS): the lane keeps the smallest value, its
 //      member and the second smallest; the pair's own d^2 is then evaluated
 //      exactly and accepted when it does not exceed the second smallest
-//      bound.  The few other members are searched exactly.
+//      bound.  The few other members are searched exactly; where they are
+//      many, or the node percolates, every pair is evaluated, here and in 5.
 //   4. l^2 = k-th smallest d^2 by a 4-pass 8-bit radix select in LDS
 //   5. links: the same products over the members with d_i^2 <= l^2 (others
 //      cannot link), tiles above the diagonal; pairs whose bound admits them
@@ -34,13 +35,15 @@
 // pairs.  512^3 workload, kernel time of a step: 2048-member bucket 291 ->
 // 20 ms, 1024 338 -> 10 ms, 256 59 -> 4 ms; one 2048-member subtree alone on
 // its CU 2.4 -> 0.7 ms.
+#include <type_traits>
+
 #include "phase_common.h"
 
 namespace rs {
 
 // LDS scalars
 enum { SH_SP, SH_NSMALL, SH_NEXT, SH_NC, SH_NCH, SH_BASE, SH_OK, SH_TOT, SH_BUCKET, SH_KK,
-       SH_NOWRAP, SH_N };
+       SH_NOWRAP, SH_NQ, SH_N };
 
 // a pushed node: members perm[s0, s0 + size), ref = member of smallest index,
 // depth below the workgroup's item (whose own level has no such bound; every
@@ -53,7 +56,15 @@ struct StackEntry {
 constexpr int WAVE_MAX = 64;      // nodes one wavefront splits by itself
 constexpr int QCAP = 128;         // queued pairs per wavefront
 constexpr int N_ROWS = 7;         // X of x y z u v w, squared norm
-constexpr float NORM_WIDE = 1e29f;
+// The screening decides next to nothing where nearest distances are tied
+// (lattices, coinciding members) or tiny beside the node (two compact clumps
+// far apart).  With more than half of the members undecided, every pair is
+// evaluated instead, as for a node that percolates: a listed member costs a
+// wavefront a pass over the node, all pairs together less than a listed half.
+// 195 nodes of 2048 members, listed one by one and this way: lattices 3.4 and
+// 2.1 ms, two clumps 4.1 and 2.0, points of a uniform box 6.3 and 2.7; sets with
+// a third of duplicates 1.9, with the limit at an eighth 2.4.
+constexpr int EXACT_PART = 2;
 
 constexpr int n_stride(int maxn) { return maxn + 16; }   // rows on different banks
 
@@ -284,6 +295,13 @@ k_wave_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, Nod
                        __builtin_amdgcn_readfirstlane(it.level), pp, nr, deepest);
 }
 
+// v, unknown to the compiler: what the exact evaluation derives from it is not
+// kept in registers through the rest of the kernel (8 to 10 fewer spilled)
+RS_DEV int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 template <int MAXN, int NT, bool FEAT>
 __global__ void __launch_bounds__(NT, 4)
 k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, NodeRec nr,
@@ -317,6 +335,15 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lm = lane & 15, lk = lane >> 4;   // tile column (or row), k offset
+    // where every pair is evaluated, the rows' space holds the coordinates
+    constexpr int R = (MAXN + NT - 1) / NT;     // members per thread
+    float4* PA = reinterpret_cast<float4*>(smem);                 // [MAXN] x y z u
+    float2* PB = reinterpret_cast<float2*>(PA + MAXN);            // [MAXN] v w
+    auto exact_member = [&](int m) {
+        const float4 a = PA[m];
+        const float2 b = PB[m];
+        return Member{a.x, a.y, a.z, a.w, b.x, b.y};
+    };
 
     for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
         const SmallItem it = items[w];
@@ -346,6 +373,7 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
                 sh[SH_NC] = 0;
                 sh[SH_NCH] = 0;
                 sh[SH_NEXT] = 0;
+                sh[SH_NQ] = 0;
             }
             if (tid < 18) acc[tid] = 0;
             if (tid < 12) ext[tid] = tid < 6 ? 0xffffffffu : 0u;
@@ -504,17 +532,21 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
             // ---- 3. nearest-neighbour distances ----
             // A wavefront takes 64 members as columns (four tiles, in
             // registers) against all rows.  A key is the pair's bound with the
-            // row's number within its lane group in the low nine bits.
-            for (;;) {
-                int g = 0;
-                if (lane == 0) g = atomicAdd(sh + SH_NEXT, 1);
-                g = __builtin_amdgcn_readfirstlane(g);
-                if (g >= ng) break;
-                const int q = 64 * g + lane;
-                const int64_t gq = it.off + perm[s0 + (q < sz ? q : 0)];
-                const Member pq = load_member(mb, gq);
-                uint64_t again = __ballot(q < sz);
-                if (!wide) {
+            // row's number within its lane group in the low nine bits.  Members
+            // left undecided (ties, near ties) are listed in tmp; too many of
+            // them end the screening.
+            const int most = sz / EXACT_PART;
+            if (!wide) {
+                for (;;) {
+                    int g = 0;
+                    if (lane == 0)
+                        g = __hip_atomic_load(sh + SH_NQ, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP) > most
+                                ? ng : atomicAdd(sh + SH_NEXT, 1);
+                    g = __builtin_amdgcn_readfirstlane(g);
+                    if (g >= ng) break;
+                    const int q = 64 * g + lane;
+                    const Member pq = load_member(mb, it.off + perm[s0 + (q < sz ? q : 0)]);
                     float b0[4], b1[4];
                     int32_t k1[4], k2[4];
 #pragma unroll
@@ -584,15 +616,23 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
                     const bool ok = q < sz && row != q &&
                                     d <= (bound - lb_add) * (1.0f - lb_k) - tiny;
                     if (ok) d2[q] = d;
-                    again &= ~__ballot(ok);
+                    const uint64_t open = __ballot(q < sz && !ok);
+                    if (open) {
+                        int at = 0;
+                        if (lane == 0) at = atomicAdd(sh + SH_NQ, __builtin_popcountll(open));
+                        at = __builtin_amdgcn_readfirstlane(at);
+                        if (q < sz && !ok)
+                            tmp[at + __builtin_popcountll(open & lanemask_lt())] = (uint16_t)q;
+                    }
                 }
-                // ties, near ties and wide nodes: the member against all others
-                while (again) {
-                    const int l = __builtin_ctzll(again);
-                    again &= again - 1;
-                    const int qm = 64 * g + l;
-                    const Member pm = {lane_f(pq.x, l), lane_f(pq.y, l), lane_f(pq.z, l),
-                                       lane_f(pq.u, l), lane_f(pq.v, l), lane_f(pq.w, l)};
+                __syncthreads();
+            }
+            const int nq = sh[SH_NQ];
+            const bool exact = wide || nq > most;
+            if (!exact) {   // each listed member against all others
+                for (int t = wave; t < nq; t += NT / 64) {
+                    const int qm = tmp[t];
+                    const Member pm = load_member(mb, it.off + perm[s0 + qm]);
                     float best = __builtin_huge_valf();
                     for (int m = lane; m < sz; m += 64) {
                         const Member pr = load_member(mb, it.off + perm[s0 + m]);
@@ -602,6 +642,55 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
                     const uint32_t mn = wave_min_u32(__float_as_uint(best));
                     if (lane == 0) d2[qm] = __uint_as_float(mn);
                 }
+            } else {
+                // Every pair once, the coordinates over the rows, by the thread
+                // that holds its earlier member (d^2 is symmetric bit for bit:
+                // the differences only change sign).  The later member's minimum
+                // is gathered over the wavefront; a wavefront skips a member
+                // that none of its row precedes.
+                const int et = opaque(tid);                            // this thread,
+                const int ew = __builtin_amdgcn_readfirstlane(et & ~63);   // its wavefront's first
+                for (int m = et; m < sz; m += NT) {
+                    const Member p = load_member(mb, it.off + perm[s0 + m]);
+                    PA[m] = make_float4(p.x, p.y, p.z, p.u);
+                    PB[m] = make_float2(p.v, p.w);
+                    d2[m] = __builtin_huge_valf();
+                }
+                __syncthreads();
+                Member pi[R];
+                float best[R];
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    pi[r] = exact_member(et + r * NT < sz ? et + r * NT : 0);
+                    best[r] = __builtin_huge_valf();
+                }
+                auto scan = [&](auto wrap) {
+                    constexpr bool WRAP = decltype(wrap)::value;
+                    for (int j = ew + 1; j < sz; j++) {
+                        const Member p = exact_member(j);
+                        float rev = __builtin_huge_valf();
+#pragma unroll
+                        for (int r = 0; r < R; r++) {
+                            if (j > r * NT + ew) {   // uniform over the wavefront
+                                const float d = phase_d2<WRAP>(
+                                    pi[r].x, pi[r].y, pi[r].z, pi[r].u, pi[r].v, pi[r].w, p.x, p.y,
+                                    p.z, p.u, p.v, p.w, fa, fc, pp.L, pp.h);
+                                const bool ok = et + r * NT < j;
+                                best[r] = ok && d < best[r] ? d : best[r];
+                                rev = ok ? fminf(rev, d) : rev;
+                            }
+                        }
+                        const uint32_t mn = wave_min_u32(__float_as_uint(rev));
+                        if (lane == 0) atomicMin(reinterpret_cast<uint32_t*>(d2) + j, mn);
+                    }
+                };
+                if (nowrap) scan(std::false_type{});
+                else scan(std::true_type{});
+#pragma unroll
+                for (int r = 0; r < R; r++)
+                    if (et + r * NT < sz)
+                        atomicMin(reinterpret_cast<uint32_t*>(d2) + et + r * NT,
+                                  __float_as_uint(best[r]));
             }
             __syncthreads();
 
@@ -656,11 +745,29 @@ k_small_subtree(const SmallItem* __restrict__ items, int n_items, Members mb, No
             __syncthreads();
             for (int m = tid; m < sz; m += NT) par[m] = m;   // over d2
             __syncthreads();
-            {
+            if (exact) {   // as the nearest neighbours: each pair of active members once
+                const int nc = sh[SH_NC], et = opaque(tid);
+                const int ew = __builtin_amdgcn_readfirstlane(et & ~63);
+                Member pi[R];
+                int si[R];
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    si[r] = et + r * NT < nc ? tmp[et + r * NT] : -1;
+                    pi[r] = exact_member(max(si[r], 0));
+                }
+                for (int q = ew + 1; q < nc; q++) {
+                    const int j = tmp[q];
+                    const Member p = exact_member(j);
+#pragma unroll
+                    for (int r = 0; r < R; r++)
+                        if (si[r] >= 0 && q > et + r * NT &&
+                            member_d2(pi[r], p, nowrap, fa, fc, pp) <= l2)
+                            lds_unite(par, si[r], j);
+                }
+            } else {
                 const int nc = sh[SH_NC], ngl = (nc + 63) >> 6;
-                const float thr = wide ? NORM_WIDE
-                                       : (l2 * (1.0f + lb_k) + lb_add) *
-                                                 (nowrap ? 1.0f : 1.00001f) + tiny;
+                const float thr =
+                    (l2 * (1.0f + lb_k) + lb_add) * (nowrap ? 1.0f : 1.00001f) + tiny;
                 int qn = 0;   // queued pairs (uniform)
                 auto drain = [&](int count) {
                     __builtin_amdgcn_wave_barrier();
