@@ -127,6 +127,7 @@ struct TArgs {
     PhaseParams pp;
     int64_t nmem;            // members at this level
     XRows X;                 // their normalised coordinates
+    int32_t* crowded;        // [tiles] set where screening does not pay
 };
 
 // Absolute slack of the box lower bounds on unwrapped positions: it covers
@@ -190,6 +191,7 @@ int tile_link(const TArgs& A, int ntiles, float* d2, int32_t* par, hipStream_t s
 //   4 the queries coded +inf, capped at cap4 = REFINE_CAP2 hi^2 (+inf beyond)
 //   5 those still coded +inf, when the k-th value lies beyond cap4 too: no cap
 //   0 exactly, no cap
+// The exact searches end at distance 0 (coinciding members).
 struct NNMode {
     float cap, stop, redo;
     bool refine;
@@ -203,7 +205,7 @@ RS_DEV NNMode nn_mode(const LParam& P) {
             : P.nnmode == 4 ? above(REFINE_CAP2 * P.hi2)
             : P.nnmode == 6 ? above(REFINE_LO2 * P.lo2)
                             : __builtin_huge_valf();
-    m.stop = P.nnmode == 1 ? P.lo2 : P.nnmode == 3 ? REFINE_LO2 * P.lo2 : -1.0f;
+    m.stop = P.nnmode == 1 ? P.lo2 : P.nnmode == 3 ? REFINE_LO2 * P.lo2 : 0.0f;
     m.redo = P.nnmode == 3 || P.nnmode == 6 ? 0.0f : __builtin_huge_valf();
     m.refine = P.nnmode >= 3;
     return m;

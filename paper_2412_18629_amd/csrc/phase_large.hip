@@ -919,8 +919,9 @@ int large_level(LargeWork* w, const std::vector<ChildOut>& hn, const Members& in
         if (grow > 1024) return RS_EINTERNAL;
         RS_TRY(tree_reserve(w, w->cap_m, w->cap_nodes, grow));
     }
+    // the tiles' boxes have been reduced; their space takes the tiles' flags
     TArgs TA{w->mnode, w->tile_node, w->nodes, w->prm, w->root, w->tb, w->T, pp,
-             M, xr};
+             M, xr, reinterpret_cast<int32_t*>(w->tbox)};
     // proposer features (when requested or when a proposal is wanted)
     const bool learned = w->model != nullptr;
     if (pp.want_feat || learned) {

@@ -39,6 +39,16 @@ static_assert(TLIST >= 127 && THITS == 64, "one pass adds up to 64 leaves or pai
 // more than 32 members.  512^3, nearest and linking: none 193 + 140 ms, up to
 // 2 queries 154 + 123, 4 146 + 118, 6 145 + 117, 9 144 + 117, 14 145 + 119.
 constexpr int FEW = 6;
+// The bounds exclude little where distances are tiny beside the node's extent
+// (compact clumps far apart, below the resolution of the tree's cells), and
+// evaluating most pairs from the queue costs several times what testing all of
+// them does.  A tile is crowded when more than half of the pairs of the leaves
+// so far with the queries had to be evaluated in the nearest-neighbour search,
+// and CROWDED_MIN more: its queries are left to k_tree_nn then, and in the linking
+// its leaves are replayed.  Two such clumps of 150000 members each: nearest 130
+// -> 70 ms, linking 89 -> 30.  (Counting in the linking itself costs it 7 % where
+// most of its time goes into true links.)
+constexpr int CROWDED_MIN = 512;
 constexpr int QS = 68;        // row stride of the queries' coordinates
 
 struct TileRec {
@@ -221,6 +231,7 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
     const Members& T = A.T;
     const PhaseParams& pp = A.pp;
     const bool cull = P.cull != 0;
+    if (NN && lane == 0 && P.nnmode <= 1) A.crowded[t] = 0;   // a level's first search
     if (NN && (!cull || P.nnmode == 2)) return;
     const NNMode md = nn_mode(P);
 
@@ -362,6 +373,11 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
         NN ? -1 : ts + __ffsll((unsigned long long)amask) - 1;   // later members only
 
     int nhit = 0;
+    uint64_t adm = 0;       // of the leaves screened together those to come,
+    int nadm = 0;           // their number in all,
+    int nexact = 0;         // NN: candidates of theirs evaluated,
+    // and whether these are too many; the linking takes over what the search found
+    bool crowded = !NN && __builtin_amdgcn_readfirstlane(A.crowded[t]) != 0;
     unsigned long long npairs = 0;   // counting build only
     // the queued candidates, one per lane: linked, or taken for the minima
     auto drain = [&]() {
@@ -377,6 +393,10 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
                     unite_pair(par, p.x, p.y, pa, pb);
             }
         }
+        if constexpr (NN) {
+            nexact += nhit;
+            crowded = nexact > CROWDED_MIN + 32 * __popcll(amask) * (nadm - __popcll(adm));
+        }
         nhit = 0;
         __syncthreads();
         if constexpr (NN) {
@@ -390,8 +410,8 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
         }
     };
 
-    // Nodes that percolate (no culling): per buffered leaf, every active query is
-    // replayed against the members, on all lanes (a lane past the leaf's end
+    // Nodes that percolate (no culling) and crowded tiles: per buffered leaf, every
+    // active query is replayed against the members, on all lanes (a lane past the leaf's end
     // holds a valid member and is masked afterwards).
     auto replay = [&](int n) {
         const float qx = mload<O32>(T.x, mm), qy = mload<O32>(T.y, mm), qz = mload<O32>(T.z, mm);
@@ -465,8 +485,8 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
         // against all leaves (some 23 vector instructions, coordinates
         // broadcast from LDS) or one leaf against all queries (some 33, box
         // broadcast from its lane), whichever set is cheaper to go through.
-        uint64_t adm = 0;
         uint32_t glo = 0, ghi = 0;
+        adm = 0;
         if (23 * __popcll(amask) < 33 * n) {
             for (uint64_t left = amask; left; left &= left - 1) {
                 const int q = __builtin_ctzll(left);
@@ -503,7 +523,10 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
             }
         }
         // row operands: member start + 16 rb + lm, coordinates lk and 4 + lk
+        nadm = __popcll(adm);
+        nexact = 0;
         while (adm) {
+            if (NN && crowded) return;
             const int src = __builtin_ctzll(adm);
             adm &= adm - 1;
             const int32_t start = __builtin_amdgcn_readlane(rstart, src);
@@ -560,7 +583,7 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
             const int rank0 = __popcll(mk & lanemask_lt());
 #pragma unroll
             for (int rb = 0; rb < 4; rb++) a1[rb] = lk == 3 ? 1.0f : a1[rb];
-            for (int c0 = 0; c0 < nq; c0 += 16) {
+            for (int c0 = 0; c0 < nq && !(NN && crowded); c0 += 16) {
                 const uint32_t rank = (uint32_t)(rank0 - c0);
                 if (((mk >> lane) & 1) && rank < 16u) col[rank] = lane;
                 __builtin_amdgcn_wave_barrier();
@@ -600,14 +623,20 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
     auto process = [&](int n) {
         if (n == 0) return;   // nothing listed: no entry to read
         __syncthreads();
-        if constexpr (NN) {
+        if constexpr (!NN) {
+            if (cull && !crowded) screen(n);
+            else replay(n);
+        } else if (!crowded) {
             screen(n);
             if (nhit) drain();
+            if (crowded) {
+                if (lane == 0) A.crowded[t] = 1;
+                limit = -1.0f;
+                act = false;
+                amask = 0;
+            }
             r2 = __uint_as_float(
                 ~wave_min_u32(act ? ~__float_as_uint(fminf(best, limit)) : ~0u));
-        } else {
-            if (cull) screen(n);
-            else replay(n);
         }
     };
 
@@ -705,8 +734,8 @@ k_tile_search(TArgs A, int ntiles, int chunk, float* __restrict__ d2,
     process(nlist);
     if constexpr (NN) {
         if (valid && (!md.refine || d2[mm] == md.redo))
-            d2[mm] = best <= limit ? nn_code(md, P, best) : md.cap < __builtin_huge_valf()
-                                         ? __builtin_huge_valf() : -best;
+            d2[mm] = best <= limit ? nn_code(md, P, best)
+                     : md.cap < __builtin_huge_valf() && !crowded ? __builtin_huge_valf() : -best;
         if (CNT && lane == 0 && npairs) atomicAdd(&g_near_pairs[blockIdx.x & 63], npairs);
     } else {
         drain();
