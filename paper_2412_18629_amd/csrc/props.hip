@@ -564,7 +564,7 @@ __global__ void k_sd_level0(PrTree T, const int32_t* __restrict__ leafcnt,
 // the kind a hierarchy gives (SD_EXACT), and when an offset took an image
 // shift (SD_SHIFT).
 constexpr int SC_ROWS = 9;
-constexpr int SD_EXACT = 1, SD_SHIFT = 2;
+constexpr int SD_EXACT = 1, SD_SHIFT = 256;   // bytes 0 and 1 of a group's word
 
 struct SeedFrame {
     float c[3], u[3];
@@ -613,7 +613,11 @@ __global__ void k_sd_seeds(PrTree T, const int32_t* __restrict__ childsum,
     sc[6 * stride + q] = a;
     sc[7 * stride + q] = c;
     sc[8 * stride + q] = k0;
-    if (fl) atomicOr(flags + root[r], fl);
+    // plain stores of one value each: a group's many seeds on one address took
+    // longer as atomics than all the rest
+    uint8_t* gf = reinterpret_cast<uint8_t*>(flags + root[r]);
+    if (fl & SD_EXACT) gf[0] = 1;
+    if (fl & SD_SHIFT) gf[1] = 1;
 }
 
 // node of every work item: the last node whose first item is not after it
@@ -802,6 +806,16 @@ k_sd_assign(const float* __restrict__ x, const float* __restrict__ y,
                 bnode = seednode[pick];
                 const bool ok = best < (wrap ? bound * (1.0f - LB_WRAP) : bound);
                 again = __ballot(valid && !ok);
+                // Undecided particles one by one cost some 90 instructions and half
+                // a one per seed each, all of them together 27 a seed, but these
+                // wait for every record in turn (twice as long at 10000 seeds).
+                const int32_t ns = q1 - q0;
+                if ((int64_t)__popcll(again) * (90 + ns / 2) > 54 * (int64_t)ns) {
+                    screen = false;
+                    again = 0;
+                    best = INFINITY;
+                    bnode = 0x7fffffff;
+                }
             }
         }
         if (!screen) {
