@@ -50,14 +50,14 @@ SMALL_BYTES = 32.0
 SMALL_MAX = 2048
 # halo properties: one 24-byte record read per member of every node
 PROPS_BYTES = 24.0
-# seed assignment: one (particle, seed) test is d^2 = fl(fl(a Dx) + fl(c Dv)),
-# 19 fp32 adds, subtracts and multiplies (3 + 3 differences, 3 + 3 squares,
-# 2 + 2 sums, 2 scalings, 1 sum); no FMA by definition and no packed
-# arithmetic, so the bound is the plain vector ALU rate: 256 CUs x 4 SIMDs x
-# 16 lanes x 2.4 GHz = 39.3 T operations/s (the 157.3 TFLOP/s fp32 figure
-# counts a packed FMA as four)
-SEED_FLOPS = 19.0
-ALU_PEAK_TFLOPS = 256 * 64 * 2.4e9 / 1e12
+# seed assignment: nearly every (particle, seed) pair is only bounded, by a
+# product over eight coefficients (two 16x16x4 fp32 matrix products per 256
+# pairs, 16 operations a pair); the bound is the fp32 matrix rate, 256 CUs x
+# 256 operations x 2.4 GHz = 157.3 TFLOP/s.  (Pairs of nodes with at most eight
+# seeds, of undecided particles and of groups that are not screened are
+# evaluated in the vector unit instead; they are counted alike.)
+SEED_FLOPS = 16.0
+MFMA_F32_PEAK_TFLOPS = 256 * 256 * 2.4e9 / 1e12
 FLAGS = {"learned": rs.RS_LEARNED, "batched": rs.RS_BATCHED, "plain": rs.RS_PLAIN}
 
 # device symbol and source files of each instrumented kernel (the PMC summary
@@ -231,7 +231,9 @@ def speedups(arrs, cfg, labels, model, ms_learned):
 
 def pair_tests(arrs, cfg, form, labels, model, kernel_ms):
     """Pair tests of the searches, counted on one extra (untimed) step with
-    the counting kernel builds, per second of the timed step's kernels."""
+    the counting kernel builds, per second of the timed step's kernels.  In
+    the large-node searches a test is a pair bounded by the screening or, where
+    that is not used, evaluated."""
     rs.rs_profile_enable(False)
     rs.rs_profile_enable(2)
     one_step(arrs, cfg, form, labels, model)
@@ -267,8 +269,8 @@ def small_node_stats(tree, prof_small, steps):
 
 
 def seed_tests(tree):
-    """(particle, seed) tests of rs_seed_assign on a tree: every own particle
-    of a node with children against every seed (leaf) below that node."""
+    """(particle, seed) pairs rs_seed_assign bounds or evaluates on a tree: every
+    own particle of a node with children with every seed (leaf) below it."""
     level, parent = tree["level"].long(), tree["parent"].long()
     deepest = tree["deepest"].long()
     m = level.numel()
@@ -362,9 +364,9 @@ def hierarchy_rows(arrs, cfg, tree, reps=3, subbox=True):
                                     "member_levels": units / max(launches, 1)}},
         "seed_assign": {"ms_per_call": ms_s, "kernel_ms": sk,
                         "assigned": int((halo >= 0).sum().item()),
-                        "roofline": {"bound": "alu", "kernel": "seed_assign",
-                                     "achieved": tflops, "peak": ALU_PEAK_TFLOPS,
-                                     "unit": "TFLOP/s", "frac": tflops / ALU_PEAK_TFLOPS,
+                        "roofline": {"bound": "mfma_f32", "kernel": "seed_assign",
+                                     "achieved": tflops, "peak": MFMA_F32_PEAK_TFLOPS,
+                                     "unit": "TFLOP/s", "frac": tflops / MFMA_F32_PEAK_TFLOPS,
                                      "tests_per_call": tests,
                                      "flops_per_test": SEED_FLOPS}},
         **({"subbox": subbox_row(arrs, cfg, reps)} if subbox else {}),
