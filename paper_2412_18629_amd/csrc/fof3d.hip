@@ -710,7 +710,9 @@ static bool use_row_table(int64_t n, const Grid3& g) {
     return rows <= std::max<uint64_t>(4 * (uint64_t)n, 1u << 20);
 }
 
-// device bytes of one 3D pass (upper bounds: octants and cells <= n)
+// Device bytes of one 3D pass (upper bounds: octants and cells <= n).  Some 12
+// bytes a particle more than a pass takes: the sum decides what rs_fof3d_noalloc
+// refuses, and that limit stays where it is documented.
 size_t fof3d_bytes(int64_t n, const Grid3& g) {
     const uint64_t rows = (uint64_t)g.nc * (uint64_t)g.nc;
     size_t bytes = 0;
@@ -718,7 +720,7 @@ size_t fof3d_bytes(int64_t n, const Grid3& g) {
     add(12 * n);                            // keys and index in; then interleaved positions
     add(8 * n); add(4 * n);                 // keys out, perm
     add(12 * n);                            // sorted positions
-    add(4 * n); add(4 * n); add(4 * n); add(4 * n);   // flags + scans
+    add(4 * n); add(4 * n); add(4 * n); add(4 * n);   // octant of a slot, run counts; spare
     add(4 * (n + 1)); add(n + 1);           // octant start, bits
     add(4 * (n + 1)); add(8 * (n + 1));     // cell octant start, keys
     add(4 * n); add(4 * n);                 // parent, minidx
@@ -726,7 +728,7 @@ size_t fof3d_bytes(int64_t n, const Grid3& g) {
     const int64_t cap_heavy = n / 4 + 1024;
     add(8 * cap_heavy); add(64);            // deferred octant pairs, count
     if (use_row_table(n, g)) add(4 * (rows + 1));   // row table
-    add(sort_temp_bytes(n)); add(scan_temp_bytes(n));
+    add(sort_temp_bytes(n)); add(scan_temp_bytes(n));   // the second one spare
     add(64);                                // counters
     return bytes;
 }

@@ -20,7 +20,7 @@ constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NH * NIN, OFF_W2 = OFF_B1 + NH,
 static_assert(NPARAM == 5825, "parameter count");
 
 // Forward, and with GRAD the backward to every parameter, of a minibatch.
-// What bounds it: 3.2e4 multiply-adds per sample are little work (0.27 GFLOP
+// What bounds it: 15552 multiply-adds per sample are little work (0.13 GFLOP
 // at 4096 samples), so the time is the chain of layers and the launches.  A
 // workgroup takes 32 samples, so that 4096 of them still spread over 128
 // CUs; the layers and the weight gradients are fp32 matrix products

@@ -34,7 +34,7 @@ constexpr int THITS = 64;     // linked pairs buffered before their unions (>= 6
 static_assert(TLIST >= 127 && THITS == 64, "one pass adds up to 64 leaves or pairs");
 // A leaf that at most FEW queries admit is screened with one member per lane, a
 // query at a time (some 20 vector instructions), instead of in a 16-wide tile
-// that would be mostly empty columns (some 160 with its 32 products).  Two
+// that would be mostly empty columns (some 160 with its 8 products).  Two
 // thirds of the leaves are such in 512^3 particles, nearly all of them with
 // more than 32 members.  512^3, nearest and linking: none 193 + 140 ms, up to
 // 2 queries 154 + 123, 4 146 + 118, 6 145 + 117, 9 144 + 117, 14 145 + 119.
