@@ -164,8 +164,9 @@ int tree_refit_active(TreeBuf& tb, int32_t n_entry, const std::vector<int32_t>& 
                       const Members& T, const int32_t* mnode, const LParam* prm,
                       const PhaseParams& pp, const float* d2, hipStream_t st);
 // chunk length: whole rounds stay at least 16 so the XCDs finish together
-// (rounds of 16, 64, 256 and 1024: the NN of a 256^3 hierarchy takes 36.4,
-// 38.0, 40.3 and 44.3 ms); the longest chunk comes from the tuning table
+// (rounds of 4, 16, 64 and 256: nearest neighbours and linking of a 256^3
+// hierarchy 25.3, 24.4, 24.6 and 24.6 ms); the longest chunk comes from the
+// tuning table
 inline int xcd_chunk(int ntiles) {
     const int cap = tune_get(TUNE_XCD_CHUNK);
     int c = ntiles / (16 * XCDS);
