@@ -18,8 +18,8 @@
 //              being linked already); octant pairs in the 27-cell
 //              neighbourhood are tested with early exit on the first linked
 //              pair and skipped when already in one component.  Pairs of
-//              more than HEAVY_PAIRS member pairs are queued and tested
-//              afterwards, one wavefront per pair.  Without auto-link (grids
+//              more than HEAVY_PAIRS member pairs (or LIGHT_PAIRS, see there)
+//              are queued and tested afterwards, one wavefront per pair.  Without auto-link (grids
 //              of under three cells per axis, or octants too wide) the
 //              union-find runs over slots and every member pair is tested.
 //   5. labels: flatten, slot parents from the octant roots, smallest
@@ -285,9 +285,12 @@ struct LinkArgs {
     int32_t* parent;            // union-find over octants (auto-link) or over slots
     const int32_t* first;       // auto-link: smallest original index of each octant
     Grid3 g;
-    int2* heavy;                // deferred octant pairs (auto-link) ...
-    int32_t* n_heavy;           // ... their count (may exceed the capacity)
-    int32_t cap_heavy;
+    // deferred octant pairs (auto-link): light ones, then heavy ones, each with
+    // a count that may exceed its capacity
+    int2 *light, *heavy;
+    int32_t *n_light, *n_heavy;
+    int32_t cap_light, cap_heavy;
+    int32_t light_oct;          // light ones are deferred above this many octants
 };
 
 // Octant pairs with more than HEAVY_PAIRS member pairs are deferred to a
@@ -298,7 +301,26 @@ struct LinkArgs {
 // the queue fills, the largest pairs no longer find room, and single threads
 // test them (6M clustered particles, link length one mean spacing: 4.5 ms,
 // with a limit of 128 213 ms).
-constexpr int64_t HEAVY_PAIRS = 1024;
+//
+// While the octants do not fill the chip many times over, the pass ends with its
+// slowest thread, and pairs above LIGHT_PAIRS are deferred as well, to a queue of
+// their own: up to LIGHT_MOST_OCT octants that hold fewer than LIGHT_CROWD
+// particles on average (32768 clustered particles 302 -> 211 us, 250k 0.57 -> 0.39
+// ms, 1M 0.90 -> 0.65, a sub-box of 500k 0.77 -> 0.55).  Where they hold more, the
+// deferred pairs are those that would have joined the rest (4M particles, link
+// length 0.6 mean spacings: 1.9 ms, with them deferred 3.2); with more octants
+// the slow threads are hidden (30M particles 13.05 ms, with them deferred 13.9).
+// One queue for both kinds left no room for the heavy ones (2M particles, one
+// mean spacing: 203 ms).
+constexpr int32_t HEAVY_PAIRS = 1024;
+constexpr int32_t LIGHT_PAIRS = 128, LIGHT_MOST_OCT = 1 << 22;
+constexpr int64_t LIGHT_CROWD = 2;
+
+// Room in the queue of heavy pairs: nearly all that there can be (pairs of
+// octants of more than 32 members on average, up to 62 for each).  With n/4
+// entries a dense clump filled it, and single threads tested the rest (60000
+// particles 17.4 -> 1.0 ms, 1M 67 -> 1.2 ms).
+static int64_t heavy_room(int64_t n) { return n / 4 + 1024 + 9 * n / 8; }
 
 // cells of row rr (cell indices [b, e))
 RS_DEV void row_cells(const LinkArgs& A, uint64_t rr, int32_t& b, int32_t& e) {
@@ -372,7 +394,8 @@ __device__ unsigned long long g_3d_pairs[64];
 
 template <bool AUTOLINK, bool PER, bool CNT>
 RS_DEV void link_cell(const LinkArgs& A, int32_t a, int32_t s0, int32_t s1, int oa, int32_t c,
-                      int dx, int dy, int dz, int32_t& ra, unsigned long long& npairs) {
+                      int dx, int dy, int dz, int32_t light_pairs, int32_t& ra,
+                      unsigned long long& npairs) {
     const Grid3& g = A.g;
     const int32_t b0 = A.cell_oct[c], b1 = A.cell_oct[c + 1];
     // an octant pair is skipped when the filter puts it beyond reach
@@ -421,10 +444,18 @@ RS_DEV void link_cell(const LinkArgs& A, int32_t a, int32_t s0, int32_t s1, int 
                 __hip_atomic_store(A.parent + b, rb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (ra == rb) continue;
             const int32_t t0 = A.oct_start[b], t1 = A.oct_start[b + 1];
-            if ((int64_t)(s1 - s0) * (t1 - t0) > HEAVY_PAIRS) {
+            const int64_t work = (int64_t)(s1 - s0) * (t1 - t0);
+            // one branch per counter: the lanes' additions to one address become one
+            if (work > HEAVY_PAIRS) {
                 const int32_t q = atomicAdd(A.n_heavy, 1);
                 if (q < A.cap_heavy) {
                     A.heavy[q] = make_int2(a, b);
+                    continue;
+                }
+            } else if (work > light_pairs) {
+                const int32_t q = atomicAdd(A.n_light, 1);
+                if (q < A.cap_light) {
+                    A.light[q] = make_int2(a, b);
                     continue;
                 }
             }
@@ -464,7 +495,9 @@ constexpr int32_t SPLIT_OCT = 1 << 18, SPLIT_DENSE = 1 << 21;
 template <bool AUTOLINK, bool PER, bool CNT, bool SPLIT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k_link(LinkArgs A) {
     const int32_t a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= A.counts[0] || *A.err) return;
+    const int32_t n_oct = A.counts[0];
+    if (a >= n_oct || *A.err) return;
+    const int32_t light_pairs = n_oct > A.light_oct ? LIGHT_PAIRS : HEAVY_PAIRS;
     unsigned long long npairs = 0;   // counting build only
     const Grid3& g = A.g;
     const int32_t s0 = A.oct_start[a], s1 = A.oct_start[a + 1];
@@ -513,7 +546,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                     if (nkey > khi) break;
                     if (nkey < cell) continue;
                     link_cell<AUTOLINK, PER, CNT>(A, a, s0, s1, oa, c, (int)(nkey - klo) - 1,
-                                                  dy, dz, ra, npairs);
+                                                  dy, dz, light_pairs, ra, npairs);
                 }
             } else {
                 for (int dx = dx0; dx <= dx1; dx++) {
@@ -524,8 +557,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) k
                     if (nkey < cell) continue;
                     const int32_t c = lower_bound_u64(A.cell_key, rb, re, nkey);
                     if (c < re && A.cell_key[c] == nkey)
-                        link_cell<AUTOLINK, PER, CNT>(A, a, s0, s1, oa, c, dx, dy, dz, ra,
-                                                      npairs);
+                        link_cell<AUTOLINK, PER, CNT>(A, a, s0, s1, oa, c, dx, dy, dz,
+                                                      light_pairs, ra, npairs);
                 }
             }
         }
@@ -549,33 +582,49 @@ template <bool PER, bool CNT>
 __global__ void __launch_bounds__(64) k_link_heavy(LinkArgs A) {
     const int lane = threadIdx.x;
     unsigned long long npairs = 0;   // counting build only
-    const int32_t nq = min(*A.n_heavy, A.cap_heavy);   // none when *A.err is set
+    // none when *A.err is set; the light ones first, which join most of the rest
+    const int32_t nl = min(*A.n_light, A.cap_light);
+    const int64_t nq = (int64_t)nl + min(*A.n_heavy, A.cap_heavy);
     const Grid3& g = A.g;
-    for (int32_t q = blockIdx.x; q < nq; q += gridDim.x) {
-        const int2 pr = A.heavy[q];
-        const int32_t ra = oct_find(A.parent, pr.x), rb = oct_find(A.parent, pr.y);
-        if (__builtin_amdgcn_readfirstlane(ra) == __builtin_amdgcn_readfirstlane(rb)) continue;
-        const int32_t s0 = A.oct_start[pr.x], s1 = A.oct_start[pr.x + 1];
-        const int32_t t0 = A.oct_start[pr.y], t1 = A.oct_start[pr.y + 1];
-        bool hit = false;
-        int steps = 0;
-        for (int32_t i = s0; i < s1 && !hit; i++) {
-            if (steps >= HEAVY_RECHECK) {
-                if (__builtin_amdgcn_readfirstlane(uf_root(A.parent, ra)) ==
-                    __builtin_amdgcn_readfirstlane(uf_root(A.parent, rb)))
-                    break;
-                steps = 0;
-            }
-            const float xi = A.sx[i], yi = A.sy[i], zi = A.sz[i];
-            for (int32_t j0 = t0; j0 < t1 && !hit; j0 += 64, steps++) {
-                const int32_t j = j0 + lane;
-                const bool near = j < t1 && link_d2<PER>(xi, yi, zi, A.sx[j], A.sy[j],
-                                                         A.sz[j], g) <= g.ll2;
-                if (CNT) npairs += (unsigned long long)min(64, t1 - j0);
-                hit = __ballot(near) != 0;
-            }
+    // each lane looks at one of the wavefront's next 64 pairs; those that are in
+    // two components still are looked at again and searched one by one
+    for (int64_t q0 = blockIdx.x; q0 < nq; q0 += 64ll * gridDim.x) {
+        const int64_t q = q0 + (int64_t)lane * gridDim.x;
+        int2 mine = make_int2(0, 0);
+        bool open = false;
+        if (q < nq) {
+            mine = q < nl ? A.light[q] : A.heavy[q - nl];
+            open = oct_find(A.parent, mine.x) != oct_find(A.parent, mine.y);
         }
-        if (hit && lane == 0) oct_unite(A.parent, A.first, ra, rb);
+        for (uint64_t todo = __ballot(open); todo; todo &= todo - 1) {
+            const int src = __builtin_ctzll(todo);
+            const int32_t pa = __builtin_amdgcn_readlane(mine.x, src);
+            const int32_t pb = __builtin_amdgcn_readlane(mine.y, src);
+            const int32_t ra = __builtin_amdgcn_readfirstlane(oct_find(A.parent, pa));
+            const int32_t rb = __builtin_amdgcn_readfirstlane(oct_find(A.parent, pb));
+            if (ra == rb) continue;
+            const int32_t s0 = A.oct_start[pa], s1 = A.oct_start[pa + 1];
+            const int32_t t0 = A.oct_start[pb], t1 = A.oct_start[pb + 1];
+            bool hit = false;
+            int steps = 0;
+            for (int32_t i = s0; i < s1 && !hit; i++) {
+                if (steps >= HEAVY_RECHECK) {
+                    if (__builtin_amdgcn_readfirstlane(uf_root(A.parent, ra)) ==
+                        __builtin_amdgcn_readfirstlane(uf_root(A.parent, rb)))
+                        break;
+                    steps = 0;
+                }
+                const float xi = A.sx[i], yi = A.sy[i], zi = A.sz[i];
+                for (int32_t j0 = t0; j0 < t1 && !hit; j0 += 64, steps++) {
+                    const int32_t j = j0 + lane;
+                    const bool near = j < t1 && link_d2<PER>(xi, yi, zi, A.sx[j], A.sy[j],
+                                                             A.sz[j], g) <= g.ll2;
+                    if (CNT) npairs += (unsigned long long)min(64, t1 - j0);
+                    hit = __ballot(near) != 0;
+                }
+            }
+            if (hit && lane == 0) oct_unite(A.parent, A.first, ra, rb);
+        }
     }
     if (CNT && lane == 0 && npairs) atomicAdd(&g_3d_pairs[blockIdx.x & 63], npairs);
 }
@@ -710,8 +759,8 @@ static bool use_row_table(int64_t n, const Grid3& g) {
     return rows <= std::max<uint64_t>(4 * (uint64_t)n, 1u << 20);
 }
 
-// Device bytes of one 3D pass (upper bounds: octants and cells <= n).  Some 12
-// bytes a particle more than a pass takes: the sum decides what rs_fof3d_noalloc
+// Device bytes of one 3D pass (upper bounds: octants and cells <= n).  About a
+// byte a particle more than a pass takes: the sum decides what rs_fof3d_noalloc
 // refuses, and that limit stays where it is documented.
 size_t fof3d_bytes(int64_t n, const Grid3& g) {
     const uint64_t rows = (uint64_t)g.nc * (uint64_t)g.nc;
@@ -720,13 +769,13 @@ size_t fof3d_bytes(int64_t n, const Grid3& g) {
     add(12 * n);                            // keys and index in; then interleaved positions
     add(8 * n); add(4 * n);                 // keys out, perm
     add(12 * n);                            // sorted positions
-    add(4 * n); add(4 * n); add(4 * n); add(4 * n);   // octant of a slot, run counts; spare
+    // octant of a slot, run counts, light pairs, the heavy ones' longer queue
+    add(4 * n); add(4 * n); add(4 * n); add(4 * n);
     add(4 * (n + 1)); add(n + 1);           // octant start, bits
     add(4 * (n + 1)); add(8 * (n + 1));     // cell octant start, keys
     add(4 * n); add(4 * n);                 // parent, minidx
     add(4 * (n + 1));                       // octant union-find
-    const int64_t cap_heavy = n / 4 + 1024;
-    add(8 * cap_heavy); add(64);            // deferred octant pairs, count
+    add(8 * (n / 4 + 1024)); add(64);       // deferred octant pairs
     if (use_row_table(n, g)) add(4 * (rows + 1));   // row table
     add(sort_temp_bytes(n)); add(scan_temp_bytes(n));   // the second one spare
     add(64);                                // counters
@@ -784,7 +833,7 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
     const int BT = 256;
     const uint64_t rows = (uint64_t)g.nc * (uint64_t)g.nc;
     const bool row_table = use_row_table(n, g);
-    const int64_t cap_heavy = n / 4 + 1024;
+    const int64_t cap_heavy = heavy_room(n);
     const int64_t ntiles = (n + OT_TILE - 1) / OT_TILE;
     // the sort's keys and indices in share one region, which holds the
     // interleaved positions once the sort has consumed them
@@ -807,10 +856,12 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
     int32_t* minidx = take<int32_t>(ar, n);
     int32_t* poct = take<int32_t>(ar, n + 1);
     int2* heavy = take<int2>(ar, cap_heavy);
+    int2* light = take<int2>(ar, n / 4);
     int32_t* row_start = row_table ? take<int32_t>(ar, rows + 1) : nullptr;
     size_t stb = sort_temp_bytes(n);
     void* stemp = arena_take(ar, stb);
-    // counters: 0 err, 1 octants, 2 cells, 3 deferred octant pairs, 4..5 groups
+    // counters: 0 err, 1 octants, 2 cells, 3 deferred heavy octant pairs, 4..5 groups,
+    // 6 deferred light ones
     int32_t* cnt = take<int32_t>(ar, 16);
     if (!cnt) return RS_EINTERNAL;
 
@@ -847,8 +898,11 @@ int fof3d_core(const float* x, const float* y, const float* z, int64_t n, const 
         const int64_t v = atoll(e);
         if (v >= 0 && v < qcap) qcap = v;
     }
+    const int32_t light_oct =
+        max_oct <= LIGHT_MOST_OCT ? (int32_t)(n / LIGHT_CROWD) : INT32_MAX;
     LinkArgs A{oct_start, oct_bits, cell_oct, cell_key, row_start, cnt + 1, cnt, kout, sx, sy, sz,
-               g.autolink ? poct : parent, minidx, g, heavy, cnt + 3, (int32_t)qcap};
+               g.autolink ? poct : parent, minidx, g, light, heavy, cnt + 6, cnt + 3,
+               (int32_t)std::min<int64_t>(n / 4, qcap), (int32_t)qcap, light_oct};
     if (instrument) prof_begin("fof3d_link", st);
     RS_TRY(B.periodic ? link_pass<true>(A, n, max_oct, st)
                        : link_pass<false>(A, n, max_oct, st));

@@ -11,7 +11,7 @@
 // cannot exclude are evaluated exactly, 64 at a time, and united or taken for
 // the minima.
 //
-// What bounds it: vector instructions (72 % of the issue slots in the
+// What bounds it: vector instructions (four fifths of the issue slots in the
 // nearest-neighbour search), and in the linking also the union-find's
 // dependent reads.  All levels of one step, before this kernel and with it:
 //   linking          512^3 199 -> 117 ms, deeply nested 9.1M particles
