@@ -305,15 +305,18 @@ struct LinkArgs {
 // While the octants do not fill the chip many times over, the pass ends with its
 // slowest thread, and pairs above LIGHT_PAIRS are deferred as well, to a queue of
 // their own: up to LIGHT_MOST_OCT octants that hold fewer than LIGHT_CROWD
-// particles on average (32768 clustered particles 302 -> 211 us, 250k 0.57 -> 0.39
-// ms, 1M 0.90 -> 0.65, a sub-box of 500k 0.77 -> 0.55).  Where they hold more, the
+// particles on average (32768 clustered particles 298 -> 216 us, 250k 0.60 -> 0.39
+// ms, 1M 0.88 -> 0.67, sub-boxes of 500k and 2.1M 0.77 -> 0.55 and 1.30 -> 1.16).
+// Above 128 they fill the queue in large sub-boxes (1.26 ms; 4M particles, link
+// length 0.4, 2.1 -> 2.4), above 256 small boxes gain less (32768 particles 222
+// us, 1M at a link length of 0.2 0.92 ms for 0.90).  Where octants hold more, the
 // deferred pairs are those that would have joined the rest (4M particles, link
 // length 0.6 mean spacings: 1.9 ms, with them deferred 3.2); with more octants
-// the slow threads are hidden (30M particles 13.05 ms, with them deferred 13.9).
+// the slow threads are hidden (30M particles 13.05 ms, with pairs above 128 deferred 13.9).
 // One queue for both kinds left no room for the heavy ones (2M particles, one
 // mean spacing: 203 ms).
 constexpr int32_t HEAVY_PAIRS = 1024;
-constexpr int32_t LIGHT_PAIRS = 128, LIGHT_MOST_OCT = 1 << 22;
+constexpr int32_t LIGHT_PAIRS = 192, LIGHT_MOST_OCT = 1 << 22;
 constexpr int64_t LIGHT_CROWD = 2;
 
 // Room in the queue of heavy pairs: nearly all that there can be (pairs of
